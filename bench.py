@@ -36,27 +36,11 @@ HBM_PEAK_GBS = 8000.0
 # the sources they were taken on: the kernels and the library code that
 # orders their workgroups.  Reported only while those sources are unchanged;
 # the summaries live in profiles/.
-SRC_2D = ["paper_2203_01462_amd/csrc/fdtd_2d.hip", "paper_2203_01462_amd/csrc/fdtd_api.hip"]
+SRC_2D = ["paper_2203_01462_amd/csrc/fdtd_2d_multi.hip", "paper_2203_01462_amd/csrc/fdtd_api.hip"]
+SRC_BATCH = ["paper_2203_01462_amd/csrc/fdtd_2d.hip", "paper_2203_01462_amd/csrc/fdtd_api.hip"]
 SRC_3D = ["paper_2203_01462_amd/csrc/fdtd_3d.hip", "paper_2203_01462_amd/csrc/fdtd_api.hip"]
 SRC_TE = ["paper_2203_01462_amd/csrc/fdtd_te.hip", "paper_2203_01462_amd/csrc/fdtd_api.hip"]
-MEASURED_TRAFFIC = {
-    "tmz2d_2048_fp32": {"sources": SRC_2D, "sha256_16": "57cf56d54ce24ece",
-                        "fwd": 77.2e6, "adj": 81.5e6,
-                        "profile": "profiles/step2d_mix_kernel_tmz2d_2048_fp32.md"},
-    # one time step of all 64 instances = one step2d_batch_mix_kernel launch
-    "tmz2d_batch64_c4": {"sources": SRC_2D, "sha256_16": "57cf56d54ce24ece",
-                         "fwd": 500.0e6, "adj": 521.7e6,
-                         "profile": "profiles/step2d_batch_mix_kernel_tmz2d_batch64_c4.md"},
-    # one time step = the general update (forward: one step3d_general_fwd
-    # launch; adjoint: three step3d_general launches) + step3d_plain
-    "yee3d_256_fp32": {"sources": SRC_3D, "sha256_16": "fcb7428c015ddb5e",
-                       "fwd": 1302.2e6, "adj": 1337.0e6,
-                       "profile": "profiles/step3d_yee3d_256_fp32.md"},
-    # one time step = one step_te_fwd / step_te_adj launch
-    "te2d_2048_fp32": {"sources": SRC_TE, "sha256_16": "7894ca2a1bac6bae",
-                       "fwd": 161.8e6, "adj": 168.4e6,
-                       "profile": "profiles/step_te_te2d_2048_fp32.md"},
-}
+MEASURED_TRAFFIC = {}
 
 
 def sources_sha(paths):
@@ -73,10 +57,10 @@ def measured_traffic(name):
     rec = MEASURED_TRAFFIC.get(name)
     if rec is None:
         return None, None
-    # the counters were taken with the default schedules (2D: two-step
-    # blocking on; 3D: off)
+    # the counters were taken with the default schedules (2D: several steps
+    # per launch; 3D: one)
     tb = os.environ.get("FDTD_TEMPORAL_BLOCKING", "")
-    if (tb == "0" and rec["sources"] is SRC_2D) or (tb == "1" and rec["sources"] is SRC_3D):
+    if (tb == "0" and rec["sources"] in (SRC_2D, SRC_BATCH)) or (tb == "1" and rec["sources"] is SRC_3D):
         return None, None
     try:
         h = sources_sha(rec["sources"])
@@ -386,7 +370,7 @@ def main():
                 "measured_gbs": round(traffic / step_s / 1e9, 1) if traffic else None,
                 "measured_frac": round(traffic / step_s / 1e9 / HBM_PEAK_GBS, 4) if traffic else None,
                 "kernel": ("step_te_fwd / step_te_adj (one launch per time step)" if W.is_te(base)
-                           else "step2d_mix_kernel (two launches per two time steps)" if base["dims"] == 2
+                           else "step2d_multi (several time steps per launch)" if base["dims"] == 2
                            else "step3d_general_fwd (forward) or step3d_general x3 (adjoint) + step3d_plain"
                                 " (one time step)"),
                 "bytes_per_step_fwd": bf, "bytes_per_step_adj": ba,

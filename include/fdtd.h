@@ -219,12 +219,13 @@ fdtd_status fdtd_destroy(fdtd_ctx *ctx);
 
 /* ------------------------------------------------------------------------
  * Batches of 2D instances.  Uneven TMz problems (own grid size, density,
- * damping, band, objective) advance together: at temporal-block depth 1 each
- * time step of all instances is one launch per tile depth in use; at depth 2
- * the instances follow the blocked schedule of a single context (plain
- * background super-tiles advance two steps per pass, everything else one
- * step per launch, two launches per pair of steps for all instances
- * together).  The N steps of a forward (or adjoint) solve are captured once
+ * damping, band, objective) advance together.  In FP64 with the depths left to
+ * the library (rows = 0, depth = 0) every launch advances all instances
+ * several steps, as a single context does.  Otherwise, at temporal-block depth
+ * 1 each time step of all instances is one launch per tile depth in use; at
+ * depth 2 the plain background's super-tiles advance two steps per pass,
+ * everything else one step per launch, two launches per pair of steps for all
+ * instances together.  The N steps of a forward (or adjoint) solve are captured once
  * into a HIP graph and replayed.  Every instance computes exactly what a
  * single context with the same config and tile depth computes.
  */
@@ -232,15 +233,18 @@ typedef struct fdtd_batch fdtd_batch; /* opaque */
 
 typedef struct {
   int32_t rows;       /* nodes per thread along y in the 2D step (tile depth):
-                         1, 2 or 4 for every instance; 0 = tune on the batch at
-                         creation: time 20 batched steps at each uniform depth,
+                         1, 2 or 4 for every instance; 0 = the library's choice:
+                         in FP64 with depth 0 several steps per launch, else
+                         tuned on the batch at creation: time 20 batched steps at each uniform depth,
                          then try the other depths for each grid size in turn
                          and keep what is faster */
   int32_t use_graph;  /* 1: replay the captured step sequence; 0: launch eagerly */
   int32_t depth;      /* temporal-block depth: 1 = one step per launch; 2 = the
                          blocked schedule for every instance that has
                          plain-background super-tiles (needs rows 0 or 2; the
-                         tile depth is then 2); 0 = tune at creation: time the
+                         tile depth is then 2); 0 = the library's choice: in FP64
+                         with rows 0 several steps per launch, else tuned at
+                         creation: time the
                          best depth-1 choice against depth 2, try depth 1 for
                          each grid size in turn inside the blocked schedule,
                          keep what is faster */
@@ -268,11 +272,13 @@ fdtd_status fdtd_batch_adjoint(fdtd_batch *b);
 /* dF/drho of instance `index` (as fdtd_gradient). */
 fdtd_status fdtd_batch_gradient(fdtd_batch *b, int32_t index, void *grad_out, int64_t count, int32_t on_device);
 
-/* Tile depth used for instance `index`, and the event time (ms) of the last
+/* Tile depth used for instance `index` (2 with several steps per launch), and
+ * the event time (ms) of the last
  * batched forward and adjoint step sequences (all instances together). */
 fdtd_status fdtd_batch_info(fdtd_batch *b, int32_t index, int32_t *rows_out, double *forward_ms, double *adjoint_ms);
 
-/* Temporal-block depth (1 or 2) used for instance `index`. */
+/* Temporal-block depth (1 or 2) used for instance `index`; with several steps
+ * per launch 2 when it has super-tiles. */
 fdtd_status fdtd_batch_depth(fdtd_batch *b, int32_t index, int32_t *depth_out);
 
 /* Release the batch and all instances.  NULL is accepted. */

@@ -1,7 +1,11 @@
 // fdtd_2d.hip -- fused time step of the 2D TMz Drude-FDTD solve and of its
-// adjoint: one launch per time step (step2d_kernel), or, with two-step
-// blocking of the plain background, two launches per two time steps
-// (step2d_mix_kernel, see the two-step section below).
+// adjoint, one launch per time step (step2d_kernel), and of batches at fixed
+// depths: one launch per step, or two launches per two time steps with
+// two-step blocking of the plain background (step2d_batch_mix_kernel).
+// Single contexts, and FP64 batches that leave the depths to the library, take
+// several steps per launch (fdtd_2d_multi.hip); the kernels here remain for
+// FP32 batches, batches that ask for a depth, contexts created with several
+// steps per launch switched off, and fields beyond 32-bit indices.
 //
 // Per step (Sec. 3.2 staggering: E, J at integer steps, H at half steps):
 //   H^{n+1/2} = H^{n-1/2} - dt/mu0 curl E^n                 (eq. (10c), CPML, TFSF)
@@ -115,6 +119,41 @@ __device__ __forceinline__ bool wave_is_edge(const int nx, const int ny, const i
   return hit(y0, y1, ja - 1) || hit(y0, y1, ja) || hit(y0, y1, jbt) || hit(y0, y1, jbt + 1);
 }
 
+// Roundings.  FP64: those of the several-step kernel, written out (fdtd_2d.hpp),
+// so that a batch and a single context agree to the last bit.  FP32: left to
+// the compiler, which contracts each of these kernels in its own way (batches
+// and single contexts differ by ~1e-8 of F).
+template <typename T>
+__device__ __forceinline__ T addm(T c, T a, T b) {  // c + a b
+  if constexpr (sizeof(T) == 8) return fma1(a, b, c);
+  else return c + a * b;
+}
+template <typename T>
+__device__ __forceinline__ T subm(T c, T a, T b) {  // c - a b
+  if constexpr (sizeof(T) == 8) return fma1(-a, b, c);
+  else return c - a * b;
+}
+template <typename T>
+__device__ __forceinline__ T mulm(T a, T b, T c) {  // a b + c
+  if constexpr (sizeof(T) == 8) return fma1(a, b, c);
+  else return a * b + c;
+}
+template <typename T>
+__device__ __forceinline__ T memm(T b, T m, T a, T v) {  // b m + a v
+  if constexpr (sizeof(T) == 8) return mem1(b, m, a, v);
+  else return b * m + a * v;
+}
+template <typename T>
+__device__ __forceinline__ T addi(T h, T a, T b) {  // h + a b, an incident term
+  if constexpr (sizeof(T) == 8) return h + mul1(a, b);
+  else return h + a * b;
+}
+template <typename T>
+__device__ __forceinline__ T subi(T h, T a, T b) {
+  if constexpr (sizeof(T) == 8) return h - mul1(a, b);
+  else return h - a * b;
+}
+
 // Does the wavefront's 64 x R block of E nodes meet the box [x0,x0+nx) x [y0,y0+ny)?
 template <int R>
 __device__ __forceinline__ bool wave_touches_box(const int i0, const int jb, const int x0, const int y0, const int bnx,
@@ -150,15 +189,15 @@ __device__ __forceinline__ void step_bulk(const Step2D<T> &p, const int par, con
   const T ch = p.chx, ce = p.ce_s;
   T hxn[R + 1];
 #pragma unroll
-  for (int r = 0; r < R + 1; ++r) hxn[r] = hx[r] - ch * (e[r + 1] - e[r]);
+  for (int r = 0; r < R + 1; ++r) hxn[r] = subm(hx[r], ch, e[r + 1] - e[r]);
 #pragma unroll
   for (int r = 0; r < R; ++r) {
     const size_t q = q0 + (size_t)r * pitch;
-    const T h = hy[r] + ch * (er[r] - e[r + 1]);
-    const T hl = hyl[r] + ch * (e[r + 1] - el[r]);
+    const T h = addm(hy[r], ch, er[r] - e[r + 1]);
+    const T hl = addm(hyl[r], ch, e[r + 1] - el[r]);
     hxw[q] = hxn[r + 1];
     hyw[q] = h;
-    ezw[q] = e[r + 1] + ce * ((h - hl) - (hxn[r + 1] - hxn[r]));
+    ezw[q] = addm(e[r + 1], ce, (h - hl) - (hxn[r + 1] - hxn[r]));
   }
 }
 
@@ -273,13 +312,13 @@ __device__ __forceinline__ void step_general(const Step2D<T> &p, const int n, co
       if (colx && j >= 0 && j <= ny - 2) {
         const T dE = e[r + 1] - e[r];
         if (pml_h(j, ny, P)) {
-          ps = gp<G>(p.byh)[j] * phx[r] + gp<G>(p.ayh)[j] * dE;
-          h = hx[r] - p.chx * (dE * gp<G>(p.ikyh)[j] + ps);
+          ps = memm(gp<G>(p.byh)[j], phx[r], gp<G>(p.ayh)[j], dE);
+          h = subm(hx[r], p.chx, mulm(dE, gp<G>(p.ikyh)[j], ps));
         } else {
-          h = hx[r] - p.chx * dE;
+          h = subm(hx[r], p.chx, dE);
         }
-        if (tfx && j == p.ja - 1) h += p.chx * eA;
-        if (tfx && j == p.jb) h -= p.chx * eB;
+        if (tfx && j == p.ja - 1) h = addi(h, p.chx, eA);
+        if (tfx && j == p.jb) h = subi(h, p.chx, eB);
       }
       hxv[r] = h;
       hxn[r] = h;
@@ -294,24 +333,24 @@ __device__ __forceinline__ void step_general(const Step2D<T> &p, const int n, co
         if (coly) {
           const T dE = er[r] - e[r + 1];
           if (pxh) {
-            ps = gp<G>(p.bxh)[i] * phy[r] + gp<G>(p.axh)[i] * dE;
-            h = hy[r] + p.chx * (dE * gp<G>(p.ikxh)[i] + ps);
+            ps = memm(gp<G>(p.bxh)[i], phy[r], gp<G>(p.axh)[i], dE);
+            h = addm(hy[r], p.chx, mulm(dE, gp<G>(p.ikxh)[i], ps));
           } else {
-            h = hy[r] + p.chx * dE;
+            h = addm(hy[r], p.chx, dE);
           }
-          if (tfr && i == p.ia - 1) h -= p.chx * einc_r[r];
-          if (tfr && i == p.ib) h += p.chx * einc_r[r];
+          if (tfr && i == p.ia - 1) h = subm(h, p.chx, einc_r[r]);
+          if (tfr && i == p.ib) h = addm(h, p.chx, einc_r[r]);
         }
         if (hasl) {
           const T dE = e[r + 1] - el[r];
           if (pxhl) {
-            const T psl = gp<G>(p.bxh)[i - 1] * phyl[r] + gp<G>(p.axh)[i - 1] * dE;
-            hl = hyl[r] + p.chx * (dE * gp<G>(p.ikxh)[i - 1] + psl);
+            const T psl = memm(gp<G>(p.bxh)[i - 1], phyl[r], gp<G>(p.axh)[i - 1], dE);
+            hl = addm(hyl[r], p.chx, mulm(dE, gp<G>(p.ikxh)[i - 1], psl));
           } else {
-            hl = hyl[r] + p.chx * dE;
+            hl = addm(hyl[r], p.chx, dE);
           }
-          if (tfr && i - 1 == p.ia - 1) hl -= p.chx * einc_r[r];
-          if (tfr && i - 1 == p.ib) hl += p.chx * einc_r[r];
+          if (tfr && i - 1 == p.ia - 1) hl = subm(hl, p.chx, einc_r[r]);
+          if (tfr && i - 1 == p.ib) hl = addm(hl, p.chx, einc_r[r]);
         }
       }
       hyv[r] = h;
@@ -327,8 +366,8 @@ __device__ __forceinline__ void step_general(const Step2D<T> &p, const int n, co
       gy[r] = e[r];
       peyn[r] = T(0);
       if (j >= 0 && j < ny && pml_e(j, ny, P)) {
-        peyn[r] = gp<G>(p.bye)[j] * pey[r] + gp<G>(p.aye)[j] * e[r];
-        gy[r] = e[r] * gp<G>(p.ikye)[j] + peyn[r];
+        peyn[r] = memm(gp<G>(p.bye)[j], pey[r], gp<G>(p.aye)[j], e[r]);
+        gy[r] = mulm(e[r], gp<G>(p.ikye)[j], peyn[r]);
       }
     }
 #pragma unroll
@@ -336,22 +375,22 @@ __device__ __forceinline__ void step_general(const Step2D<T> &p, const int n, co
       gx[r] = e[r + 1];
       pexn[r] = T(0);
       if (pxe) {
-        pexn[r] = gp<G>(p.bxe)[i] * pex[r] + gp<G>(p.axe)[i] * e[r + 1];
-        gx[r] = e[r + 1] * gp<G>(p.ikxe)[i] + pexn[r];
+        pexn[r] = memm(gp<G>(p.bxe)[i], pex[r], gp<G>(p.axe)[i], e[r + 1]);
+        gx[r] = mulm(e[r + 1], gp<G>(p.ikxe)[i], pexn[r]);
       }
-      gxr[r] = pxer ? er[r] * gp<G>(p.ikxe)[i + 1] + (gp<G>(p.bxe)[i + 1] * pexr[r] + gp<G>(p.axe)[i + 1] * er[r]) : er[r];
-      gxl[r] = pxel ? el[r] * gp<G>(p.ikxe)[i - 1] + (gp<G>(p.bxe)[i - 1] * pexl[r] + gp<G>(p.axe)[i - 1] * el[r]) : el[r];
+      gxr[r] = pxer ? mulm(er[r], gp<G>(p.ikxe)[i + 1], memm(gp<G>(p.bxe)[i + 1], pexr[r], gp<G>(p.axe)[i + 1], er[r])) : er[r];
+      gxl[r] = pxel ? mulm(el[r], gp<G>(p.ikxe)[i - 1], memm(gp<G>(p.bxe)[i - 1], pexl[r], gp<G>(p.axe)[i - 1], el[r])) : el[r];
     }
 #pragma unroll
     for (int r = 0; r < R + 1; ++r) {
       const int j = jb - 1 + r;
       T h = T(0), g = T(0), nu = T(0);
       if (colx && j >= 0 && j <= ny - 2) {
-        h = hx[r] - p.chx * (gy[r + 1] - gy[r]);
+        h = subm(hx[r], p.chx, gy[r + 1] - gy[r]);
         g = h;
         if (pml_h(j, ny, P)) {
-          nu = gp<G>(p.byh)[j] * phx[r] + gp<G>(p.ayh)[j] * h;
-          g = h * gp<G>(p.ikyh)[j] + nu;
+          nu = memm(gp<G>(p.byh)[j], phx[r], gp<G>(p.ayh)[j], h);
+          g = mulm(h, gp<G>(p.ikyh)[j], nu);
         }
       }
       hxn[r] = h;
@@ -364,17 +403,17 @@ __device__ __forceinline__ void step_general(const Step2D<T> &p, const int n, co
       T h = T(0), g = T(0), gl = T(0), nu = T(0);
       if (j >= 1 && j <= ny - 2) {
         if (coly) {
-          h = hy[r] + p.chx * (gxr[r] - gx[r]);
+          h = addm(hy[r], p.chx, gxr[r] - gx[r]);
           g = h;
           if (pxh) {
-            nu = gp<G>(p.bxh)[i] * phy[r] + gp<G>(p.axh)[i] * h;
-            g = h * gp<G>(p.ikxh)[i] + nu;
+            nu = memm(gp<G>(p.bxh)[i], phy[r], gp<G>(p.axh)[i], h);
+            g = mulm(h, gp<G>(p.ikxh)[i], nu);
           }
         }
         if (hasl) {
-          const T hl = hyl[r] + p.chx * (gx[r] - gxl[r]);
+          const T hl = addm(hyl[r], p.chx, gx[r] - gxl[r]);
           gl = hl;
-          if (pxhl) gl = hl * gp<G>(p.ikxh)[i - 1] + (gp<G>(p.bxh)[i - 1] * phyl[r] + gp<G>(p.axh)[i - 1] * hl);
+          if (pxhl) gl = mulm(hl, gp<G>(p.ikxh)[i - 1], memm(gp<G>(p.bxh)[i - 1], phyl[r], gp<G>(p.axh)[i - 1], hl));
         }
       }
       hyn[r] = h;
@@ -398,12 +437,12 @@ __device__ __forceinline__ void step_general(const Step2D<T> &p, const int n, co
     if (!ADJ) {
       T cx = dHy, cy = dHx;
       if (pxe) {
-        pexf[r] = gp<G>(p.bxe)[i] * pex[r] + gp<G>(p.axe)[i] * dHy;
-        cx = dHy * gp<G>(p.ikxe)[i] + pexf[r];
+        pexf[r] = memm(gp<G>(p.bxe)[i], pex[r], gp<G>(p.axe)[i], dHy);
+        cx = mulm(dHy, gp<G>(p.ikxe)[i], pexf[r]);
       }
       if (pml_e(j, ny, P)) {
-        peyf[r] = gp<G>(p.bye)[j] * pey[r + 1] + gp<G>(p.aye)[j] * dHx;
-        cy = dHx * gp<G>(p.ikye)[j] + peyf[r];
+        peyf[r] = memm(gp<G>(p.bye)[j], pey[r + 1], gp<G>(p.aye)[j], dHx);
+        cy = mulm(dHx, gp<G>(p.ikye)[j], peyf[r]);
       }
       curl = cx - cy;
       if (tfx && j == p.ja) curl += hA;
@@ -420,20 +459,35 @@ __device__ __forceinline__ void step_general(const Step2D<T> &p, const int n, co
     gnew[r] = 0.0;
     if (des && !gap) {
       const T x = rr[r];
-      const T eps2 = p.A0 + x * p.A1;
-      const T beta = p.B0 + x * p.B1;
-      const T bs = beta * p.dt_ + p.Sg * x * (T(1) - x);
-      const T inv = T(2) / (eps2 + bs);
-      const T dE = inv * (p.dtdx * curl - p.dthJ * Jo[r] - bs * e0);
-      e1 = e0 + dE;
-      Jn[r] = Jo[r] + (p.kpm1 * Jo[r] + beta * (e0 + e1));  // increment form: kp - 1 ~ -gamma dt is kept exactly
+      T eps2, beta, bs, dE;
+      if constexpr (sizeof(T) == 8) {
+        eps2 = fma1(x, p.A1, p.A0);
+        beta = fma1(x, p.B1, p.B0);
+        bs = fma1(beta, p.dt_, p.Sg * x * (T(1) - x));
+        const T inv = T(2) / (eps2 + bs);
+        const T q = fma1(-bs, e0, fma1(p.dtdx, curl, -(p.dthJ * Jo[r])));
+        dE = inv * q;
+        e1 = fma1(inv, q, e0);
+        Jn[r] = Jo[r] + fma1(p.kpm1, Jo[r], beta * (e0 + e1));  // increment form: kp - 1 ~ -gamma dt is kept exactly
+      } else {
+        eps2 = p.A0 + x * p.A1;
+        beta = p.B0 + x * p.B1;
+        bs = beta * p.dt_ + p.Sg * x * (T(1) - x);
+        const T inv = T(2) / (eps2 + bs);
+        dE = inv * (p.dtdx * curl - p.dthJ * Jo[r] - bs * e0);
+        e1 = e0 + dE;
+        Jn[r] = Jo[r] + (p.kpm1 * Jo[r] + beta * (e0 + e1));  // increment form
+      }
       if (ADJ) {
         const T gc = -(T(1) - p.rs) / (T(2) * (p.rs + x * (T(1) - p.rs)));
         const T gb = p.gsm * (T(1) - T(2) * x);
-        gnew[r] = gacc[r] + (double)(Em[r] * (p.ga * dE + gb * (e0 + e1) + gc * (Jn[r] + Jo[r])));
+        if constexpr (sizeof(T) == 8)
+          gnew[r] = sens1(gacc[r], Em[r], fma1(gc, Jn[r] + Jo[r], fma1(p.ga, dE, gb * (e0 + e1))));
+        else
+          gnew[r] = gacc[r] + (double)(Em[r] * (p.ga * dE + gb * (e0 + e1) + gc * (Jn[r] + Jo[r])));
       }
     } else {
-      e1 = e0 + (gap ? p.ce_g : p.ce_s) * curl;
+      e1 = addm(e0, gap ? p.ce_g : p.ce_s, curl);
     }
     en[r] = e1;
   }
@@ -640,14 +694,14 @@ __device__ __forceinline__ void tb_block(const Step2D<T> &p, const int code, T *
   // H^{n+1/2}
   for (int e = t; e < TLY * TLX; e += NT) {
     const int r = e / TLX, c = e - r * TLX, k = r * TLS + c;
-    if (r < TLY - 1) HX[k] = HX[k] - ch * (E[k + TLS] - E[k]);
-    if (c < TLX - 1) HY[k] = HY[k] + ch * (E[k + 1] - E[k]);
+    if (r < TLY - 1) HX[k] = subm(HX[k], ch, E[k + TLS] - E[k]);
+    if (c < TLX - 1) HY[k] = addm(HY[k], ch, E[k + 1] - E[k]);
   }
   __syncthreads();
   // E^{n+1}
   for (int e = t; e < (TLY - 2) * (TLX - 2); e += NT) {
     const int r = 1 + e / (TLX - 2), c = 1 + e % (TLX - 2), k = r * TLS + c;
-    E[k] = E[k] + ce * ((HY[k] - HY[k - 1]) - (HX[k] - HX[k - TLS]));
+    E[k] = addm(E[k], ce, (HY[k] - HY[k - 1]) - (HX[k] - HX[k - TLS]));
   }
   __syncthreads();
   if (mid) {  // the intermediate state of the super-tile, for the per-step neighbours
@@ -666,37 +720,19 @@ __device__ __forceinline__ void tb_block(const Step2D<T> &p, const int code, T *
   // H^{n+3/2}
   for (int e = t; e < (TLY - 2) * (TLX - 2); e += NT) {
     const int r = 1 + e / (TLX - 2), c = 1 + e % (TLX - 2), k = r * TLS + c;
-    if (r < TLY - 2) HX[k] = HX[k] - ch * (E[k + TLS] - E[k]);
-    if (c < TLX - 2) HY[k] = HY[k] + ch * (E[k + 1] - E[k]);
+    if (r < TLY - 2) HX[k] = subm(HX[k], ch, E[k + TLS] - E[k]);
+    if (c < TLX - 2) HY[k] = addm(HY[k], ch, E[k + 1] - E[k]);
   }
   __syncthreads();
   // E^{n+2} on the super-tile, stored with the new H
   for (int e = t; e < TBY * TBX; e += NT) {
     const int r = TBH + e / TBX, c = TBH + e % TBX, k = r * TLS + c;
     const size_t q = (size_t)(y0 + r) * pitch + (x0 + c);
-    gp<G>(ezo)[q] = E[k] + ce * ((HY[k] - HY[k - 1]) - (HX[k] - HX[k - TLS]));
+    gp<G>(ezo)[q] = addm(E[k], ce, (HY[k] - HY[k - 1]) - (HX[k] - HX[k - TLS]));
     gp<G>(hxo)[q] = HX[k];
     gp<G>(hyo)[q] = HY[k];
   }
 }
-// One launch of the blocked schedule: workgroups [0, nrest) take one
-// per-step update of the tiles in ps.tlist (step n), the others two steps of
-// the super-tiles tiles[0, ntb) of the pair described by pt.
-template <typename T, bool ADJ>
-__global__ void __launch_bounds__(NT, FDTD2D_MIN_WAVES)
-    step2d_mix_kernel(const Step2D<T> ps, const int n, const int nrest, const Step2D<T> pt,
-                      const int *__restrict__ tiles, T *ezo, T *hxo, T *hyo) {
-  __shared__ T E[TLY * TLS], HX[TLY * TLS], HY[TLY * TLS];
-  const int b = blockIdx.x;
-  // per-step workgroups first: their slow design and absorber tiles start
-  // early and the two-step workgroups fill the machine around them
-  if (b < nrest) {
-    step2d_block<T, ADJ, RDEF, false>(ps, n, 0, b);
-    return;
-  }
-  tb_block<T, false>(pt, tiles[b - nrest], ezo, hxo, hyo, E, HX, HY);
-}
-
 // Last k with f[k] <= b.
 __device__ __forceinline__ int owner(const cptr2<int> f, const int ninst, const int b) {
   int lo = 0, hi = ninst - 1;
@@ -804,17 +840,6 @@ Tb2dPlan tb2d_plan(int nx, int ny, int P, int ia, int ib, int ja, int jb, const 
 }
 
 template <typename T>
-void launch_step2d_mix(const Step2D<T> &ps, int n, int nrest, const Step2D<T> &pt, const int *tiles, int ntb, T *ezo,
-                       T *hxo, T *hyo, bool adjoint, hipStream_t s) {
-  const int nb = nrest + ntb;
-  if (nb <= 0) return;
-  if (adjoint)
-    hipLaunchKernelGGL((step2d_mix_kernel<T, true>), dim3(nb), dim3(NT), 0, s, ps, n, nrest, pt, tiles, ezo, hxo, hyo);
-  else
-    hipLaunchKernelGGL((step2d_mix_kernel<T, false>), dim3(nb), dim3(NT), 0, s, ps, n, nrest, pt, tiles, ezo, hxo, hyo);
-}
-
-template <typename T>
 void launch_step2d_batch_mix(const Mix2D<T> *ds, const int *firstR, const int *firstT, int ninst, int nrest_total,
                              int nblocks, int n, bool adjoint, hipStream_t s) {
   if (nblocks <= 0) return;
@@ -849,10 +874,6 @@ void launch_step2d_batch(const Step2D<T> *ps, const int *first, int ninst, int n
   else launch_batch<T, false>(ps, first, ninst, nblocks, n, par, rows, s);
 }
 
-template void launch_step2d_mix<float>(const Step2D<float> &, int, int, const Step2D<float> &, const int *, int,
-                                       float *, float *, float *, bool, hipStream_t);
-template void launch_step2d_mix<double>(const Step2D<double> &, int, int, const Step2D<double> &, const int *, int,
-                                        double *, double *, double *, bool, hipStream_t);
 template void launch_step2d_batch_mix<float>(const Mix2D<float> *, const int *, const int *, int, int, int, int, bool,
                                              hipStream_t);
 template void launch_step2d_batch_mix<double>(const Mix2D<double> *, const int *, const int *, int, int, int, int,

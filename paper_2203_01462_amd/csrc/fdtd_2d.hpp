@@ -43,6 +43,25 @@ struct Step2D {
   const int *tlist;  // per-step launch over these workgroup tiles (ty * nbx + tx), or all when null
 };
 
+// The roundings of a node's update that the compiler could contract in more
+// than one way, written out: every kernel that computes a value (its owner,
+// and the neighbours that recompute it) then gets the same bits.
+__device__ __forceinline__ float fma1(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double fma1(double a, double b, double c) { return __builtin_fma(a, b, c); }
+// absorber memory b m + a v
+template <typename T>
+__device__ __forceinline__ T mem1(T b, T m, T a, T v) { return fma1(b, m, a * v); }
+// a b, rounded (never contracted into the sum that takes it): the incident
+// wave's share at the horizontal injection lines
+template <typename T>
+__device__ __forceinline__ T mul1(T a, T b) {
+#pragma clang fp contract(off)
+  return a * b;
+}
+// FP64 sensitivity sum g + e t
+__device__ __forceinline__ double sens1(double g, float e, float t) { return g + (double)(e * t); }
+__device__ __forceinline__ double sens1(double g, double e, double t) { return fma1(e, t, g); }
+
 // One time step; rows = nodes per thread along y (1, 2 or 4; 0 = default).
 template <typename T>
 void launch_step2d(const Step2D<T> &p, int n, int par, bool adjoint, hipStream_t s, int rows = 0);
@@ -57,7 +76,8 @@ void launch_step_te(const Step2D<T> &p, int n, bool adjoint, hipStream_t s);
 // Workgroups of one instance's step launch (rows <= 0: the default depth).
 int step2d_blocks(int nx, int ny, int rows);
 
-// Two-step blocking of the plain background.  Super-tiles of 64 x 16 nodes
+// Two-step blocking of the plain background (batches that ask for it).
+// Super-tiles of 64 x 16 nodes
 // whose reach (three nodes around them) holds only background dielectric --
 // no absorber, wall, injection line, design or gap -- advance two time steps
 // at once from an LDS copy of their tile with a two-node halo; the other
@@ -71,21 +91,13 @@ struct Tb2dPlan {
 };
 Tb2dPlan tb2d_plan(int nx, int ny, int P, int ia, int ib, int ja, int jb, const int dbox[4], const int gbox[4]);
 
-// One launch of the blocked schedule: nrest workgroups update the rest
-// tiles listed in ps.tlist by one step (step n; copy 0 read, copy 1 written),
-// ntb workgroups advance the super-tiles tiles[0..ntb) by two steps of the
-// pair described by pt (copy 0: E^m, H^{m-1/2}; copy 1 receives the border
-// super-tiles' intermediate state; ezo, hxo, hyo the state after the pair).
-// Either count may be zero.  The two-step update is the background update,
-// identical in the forward and the adjoint.
-template <typename T>
-void launch_step2d_mix(const Step2D<T> &ps, int n, int nrest, const Step2D<T> &pt, const int *tiles, int ntb, T *ezo,
-                       T *hxo, T *hyo, bool adjoint, hipStream_t s);
-
 // One instance's part of a batched launch of the blocked schedule: nrest
 // workgroups take the per-step update of the tiles in ps.tlist (the whole
 // grid when null), ntb workgroups advance tiles[0..ntb) by the pair
-// described by pt (as in launch_step2d_mix).  Parities are resolved.
+// described by pt (copy 0: E^m, H^{m-1/2}; copy 1 receives the border
+// super-tiles' intermediate state; ezo, hxo, hyo the state after the pair).
+// The two-step update is the background update, identical in the forward and
+// the adjoint.  Parities are resolved.
 template <typename T>
 struct Mix2D {
   Step2D<T> ps, pt;
@@ -102,6 +114,38 @@ struct Mix2D {
 template <typename T>
 void launch_step2d_batch_mix(const Mix2D<T> *ds, const int *firstR, const int *firstT, int ninst, int nrest_total,
                              int nblocks, int n, bool adjoint, hipStream_t s);
+
+// Several time steps per launch (fdtd_2d_multi.hip).  The parameter block of
+// an instance: both copies of every array in their fixed places (the launch
+// says which one is read), the Drude current included.
+template <typename T>
+struct Multi2D {
+  Step2D<T> s;
+  T *J[2];
+};
+
+// Regions of a launch: R rows per lane, nw wavefronts (R nw rows), K nodes of
+// halo on every side, so up to K steps per launch.
+struct MultiTile {
+  int R, nw, K;
+};
+
+// Regions for launches over `count` grids of n[k][0] x n[k][1] nodes.
+MultiTile multi2d_tile(const int (*n)[2], int count, int precision);
+
+// Workgroups of one instance in a launch.
+int step2d_multi_blocks(int nx, int ny, const MultiTile &g);
+
+// `steps` (at most g.K) time steps from step number n0 on (ascending;
+// descending in the adjoint) of `ninst` instances (device array `ms`; with
+// several, instance k from workgroup first[k] on, `nblocks` in all): copy rd
+// is read, copy rd ^ 1 written.  hist: the history buffer, holding the steps
+// from hist_base on and written by the forward when hist_on (null: each
+// instance's own).
+template <typename T>
+void launch_step2d_multi(const Multi2D<T> *ms, const int *first, int ninst, int nblocks, int n0, int steps,
+                         const MultiTile &g, int rd, bool adjoint, void *hist, int hist_base, int hist_on,
+                         hipStream_t s);
 
 // One time step of several instances (device array `ps` of their parameters,
 // `first[k]` = first workgroup of instance k, blocks of each instance padded

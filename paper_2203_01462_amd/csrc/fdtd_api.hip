@@ -43,9 +43,20 @@ struct fdtd_ctx {
   // checkpointed adjoint: a second state (both copies and J) for re-running
   // forward segments, and the snapshots [nseg-1][state copy + J]
   DevBuf fldR[2][6], pmlR[2][12], arenaR[3], JR, snap;
-  // 2D two-step blocking of the plain background: a third copy of the fields
-  // (main and re-run state), the super-tiles and the per-step tiles
-  DevBuf fld3[3], fld3R[3], tbTiles, tbRest;
+  // 2D TMz, several steps per launch (fdtd_2d_multi.hip): the second copy of
+  // the Drude current, the regions and the copy that holds the state now
+  // (main and re-run; the launches alternate between the copies)
+  bool multi = false;
+  DevBuf Jb, JRb;
+  MultiTile mt{4, 8, 4};
+  int cur[2] = {0, 0};
+  Multi2D<float> m2f[2]{};
+  Multi2D<double> m2d[2]{};
+  DevBuf mdesc;  // the two parameter blocks on the device
+  // a batch's two-step blocking of the plain background: a third copy of the
+  // fields, the super-tiles and the per-step tiles
+  DevBuf fld3[3], tbTiles, tbRest;
+  int super_tiles = 0;  // super-tiles the grid has room for (what fdtd_batch_depth reports)
   DevBuf glist3;  // 3D: tile-chunk lists of the general update
   int gS = 0, gM = 0, gD = 0, gAxD = 0;  // lengths of the three lists in glist3
   // 3D two-step blocking of the plain background (FP32): the super-chunk
@@ -89,6 +100,11 @@ struct fdtd_ctx {
 namespace {
 
 thread_local std::string g_create_error;  // per thread: creates may run on several threads
+
+// How a 2D TMz context steps: several steps per launch (single contexts, and
+// FP64 batches that leave the tile and block depths to the library), one step
+// per launch, or a batch's two-step blocked schedule.
+enum class Kind2D { kMulti, kPerStep, kBlocked };
 
 // Steps between two checks of the forward solve's watchdog.
 constexpr int kWatchEvery = 1024;
@@ -225,11 +241,12 @@ void deal_to_xcds(std::vector<int> &v, int lo, int hi, G group) {
   }
 }
 
-// Two-step blocking of the plain background, read when a context is
-// created: FDTD_TEMPORAL_BLOCKING=0 turns it off, =1 on; unset, 2D contexts
-// use it (super-tiles) and 3D contexts do not (super-chunks: bit-identical
-// but slower on the 256^3 workload, whose plain background is half the grid
-// and a third of the step time).  Both schedules give the same results.
+// Several time steps per launch, read when a context is created:
+// FDTD_TEMPORAL_BLOCKING=0 turns it off, =1 on; unset, 2D contexts use it and
+// 3D contexts do not (two steps of the plain background's super-chunks:
+// bit-identical but slower on the 256^3 workload, whose plain background is
+// half the grid and a third of the step time).  Both schedules give the same
+// results.
 bool blocking_enabled(int dims) {
   const char *v = std::getenv("FDTD_TEMPORAL_BLOCKING");
   if (v && v[0] == '0') return false;
@@ -237,7 +254,7 @@ bool blocking_enabled(int dims) {
   return dims == 2;
 }
 
-void create_2d(fdtd_ctx *c) {
+void create_2d(fdtd_ctx *c, Kind2D kind) {
   const fdtd_config &g = c->cfg;
   const int P = g.pml_cells, m = g.tfsf_margin;
   c->ia = P + m; c->ib = c->nx - 1 - P - m;
@@ -295,7 +312,14 @@ void create_2d(fdtd_ctx *c) {
   // without a plane wave there are no injection lines to keep clear
   Tb2dPlan pl = tf ? tb2d_plan(c->nx, c->ny, P, c->ia, c->ib, c->ja, c->jb, dbox, gbox)
                    : tb2d_plan(c->nx, c->ny, P, -8, -8, -8, -8, dbox, gbox);
-  if (!pl.tb.empty() && blocking_enabled(2) && !c->te) {
+  c->super_tiles = (int)pl.tb.size();
+  // (the several-step kernel indexes a field with 32 bits)
+  c->multi = !c->te && kind == Kind2D::kMulti && blocking_enabled(2) && (int64_t)c->pitch * c->ny < INT32_MAX;
+  if (c->multi) {
+    const int n2d[1][2] = {{c->nx, c->ny}};
+    c->mt = multi2d_tile(n2d, 1, c->prec);
+  }
+  if (!pl.tb.empty() && kind == Kind2D::kBlocked && blocking_enabled(2) && !c->te) {
     // the interior super-tiles run one launch early (beside the rest tiles'
     // second step of the previous pair), the border ones after them
     std::vector<int> order;
@@ -322,18 +346,21 @@ void create_2d(fdtd_ctx *c) {
     FDTD_HIP(hipMemcpy(c->tbTiles.p, order.data(), order.size() * sizeof(int), hipMemcpyHostToDevice));
     if (!pl.rest.empty())
       FDTD_HIP(hipMemcpy(c->tbRest.p, pl.rest.data(), pl.rest.size() * sizeof(int), hipMemcpyHostToDevice));
-    for (int k = 0; k < 3; ++k) {
-      c->fld3[k].alloc(n2);
-      if (c->nseg > 1) c->fld3R[k].alloc(n2);
-    }
+    for (int k = 0; k < 3; ++k) c->fld3[k].alloc(n2);
   }
 }
 
-// Field copy holding the state after `s` steps of a solve: with two-step
-// blocking three copies rotate (a pair of steps reads copy s and writes
-// copy s+2, as two single steps would), else two.  Absorber memories always
-// alternate between two copies.
-int fcopy(const fdtd_ctx *c, int s) { return c->nTb > 0 ? s % 3 : s & 1; }
+// Field copy holding the state after `s` steps of a solve: with several steps
+// per launch the copy the last launch wrote; with a batch's two-step blocking
+// three copies rotate (a pair of steps reads copy s and writes copy s+2, as
+// two single steps would); else two alternate.  Absorber memories, and the
+// Drude current of the several-step launches, have two copies.
+int fcopy(const fdtd_ctx *c, bool rerun, int s) { return c->multi ? c->cur[rerun] : c->nTb > 0 ? s % 3 : s & 1; }
+int mcopy(const fdtd_ctx *c, bool rerun, int s) { return c->multi ? c->cur[rerun] : s & 1; }
+DevBuf &jbuf(fdtd_ctx *c, bool rerun) {
+  if (c->multi && c->cur[rerun]) return rerun ? c->JRb : c->Jb;
+  return rerun ? c->JR : c->J;
+}
 
 // 3D arena holding the state after `s` steps: three rotate with two-step
 // blocking, else two.
@@ -342,7 +369,7 @@ DevBuf &arena(fdtd_ctx *c, bool rerun, int s) { return rerun ? c->arenaR[acopy(c
 
 
 DevBuf *field_buf(fdtd_ctx *c, bool rerun, int copy, int k) {
-  if (copy == 2) return rerun ? &c->fld3R[k] : &c->fld3[k];
+  if (copy == 2) return &c->fld3[k];
   return rerun ? &c->fldR[copy][k] : &c->fld[copy][k];
 }
 
@@ -521,8 +548,10 @@ void create_common(fdtd_ctx *c) {
   // history of ck steps (all N without checkpoints) plus nseg-1 snapshots
   const int hist_steps = c->nseg > 1 ? c->ck : c->N;
   const double hist_bytes = (double)hist_steps * c->nd * c->ncomp * c->esz;
+  if (c->multi) c->Jb.alloc(c->J.bytes);
   if (c->nseg > 1) {
     c->JR.alloc(c->J.bytes);
+    if (c->multi) c->JRb.alloc(c->J.bytes);
     c->snap_bytes = c->J.bytes;
     for (int b = 0; b < 1; ++b) {
       if (c->dims == 2) {
@@ -609,6 +638,8 @@ void zero_state(fdtd_ctx *c) {
     if (c->arena3[b].p) zero(c, c->arena3[b]);
   for (int k = 0; k < 3; ++k) if (c->fld3[k].p) zero(c, c->fld3[k]);
   zero(c, c->J);
+  if (c->Jb.p) zero(c, c->Jb);
+  c->cur[0] = 0;
 }
 
 // ------------------------------------------------ test-only state access
@@ -719,12 +750,12 @@ void download_state(fdtd_ctx *c, double *out) {
   const int nfe = state_efields(c);
   std::vector<std::vector<T>> img(c->dims == 2 ? 3 : 1);
   for (size_t b = 0; b < img.size(); ++b) {
-    DevBuf *src = c->dims == 2 ? field_buf(c, false, fcopy(c, c->N), (int)b) : &arena(c, false, c->N);
+    DevBuf *src = c->dims == 2 ? field_buf(c, false, fcopy(c, false, c->N), (int)b) : &arena(c, false, c->N);
     img[b].resize(src->bytes / sizeof(T));
     FDTD_HIP(hipMemcpyAsync(img[b].data(), src->p, src->bytes, hipMemcpyDeviceToHost, c->stream));
   }
   std::vector<T> jv((size_t)c->nd * c->ncomp);
-  FDTD_HIP(hipMemcpyAsync(jv.data(), c->J.p, jv.size() * sizeof(T), hipMemcpyDeviceToHost, c->stream));
+  FDTD_HIP(hipMemcpyAsync(jv.data(), jbuf(c, false).p, jv.size() * sizeof(T), hipMemcpyDeviceToHost, c->stream));
   FDTD_HIP(hipStreamSynchronize(c->stream));
   for (int f = 0; f < state_fields(c); ++f)
     for (int k = 0; k < c->nz; ++k)
@@ -770,7 +801,7 @@ template <typename T>
 Step2D<T> params2d_at(fdtd_ctx *c, bool rerun, int s, int hist_base, bool hist_on, void *hist) {
   Step2D<T> p = params2d<T>(c, rerun);
   p.hist = static_cast<T *>(hist);
-  const int fr = fcopy(c, s), fw = fcopy(c, s + 1);
+  const int fr = fcopy(c, rerun, s), fw = fcopy(c, rerun, s + 1);
   p.ez[0] = field_buf(c, rerun, fr, 0)->as<T>(); p.ez[1] = field_buf(c, rerun, fw, 0)->as<T>();
   p.hx[0] = field_buf(c, rerun, fr, 1)->as<T>(); p.hx[1] = field_buf(c, rerun, fw, 1)->as<T>();
   p.hy[0] = field_buf(c, rerun, fr, 2)->as<T>(); p.hy[1] = field_buf(c, rerun, fw, 2)->as<T>();
@@ -804,16 +835,18 @@ void launch_step(fdtd_ctx *c, bool rerun, int n, int s, bool adjoint, int hist_b
   }
 }
 
+template <typename T>
+Multi2D<T> &params_multi(fdtd_ctx *c, bool rerun);
+template <>
+Multi2D<float> &params_multi<float>(fdtd_ctx *c, bool rerun) { return c->m2f[rerun]; }
+template <>
+Multi2D<double> &params_multi<double>(fdtd_ctx *c, bool rerun) { return c->m2d[rerun]; }
+
 // `count` consecutive time steps of a solve, the first one the (s0+1)-th:
 // step j has step number nof(j), history base hbase and history flag hon(j).
-// With two-step blocking (2D, nTb > 0) the steps go in pairs, pipelined two
-// launches per pair: launch A of pair q = the rest tiles' first step of q and
-// the border super-tiles of q (all super-tiles for the first pair); launch B
-// = the rest tiles' second step of q and the interior super-tiles of pair
-// q+1, run early.  Those reach only other super-tiles, whose state after the
-// pair is already written, and write their output into the copy that the
-// rest tiles read in that launch only outside the super-tiles.  An odd last
-// step is a full-grid single step.
+// With several steps per launch (2D TMz) the block is the fewest launches,
+// their step counts as even as they go (callers' blocks never straddle a saved
+// state, so the history flag holds for a whole block).
 //
 // In 3D with super-chunks (FP32) a pair is the two-step pass over the
 // super-chunks (state after s0+2q read, after s0+2q+2 written, border nodes
@@ -850,33 +883,17 @@ void run_block(fdtd_ctx *c, bool rerun, bool adjoint, int s0, int count, NOF nof
       return;
     }
   }
-  if (c->dims != 2 || c->nTb == 0) {
-    for (int j = 0; j < count; ++j) launch_step<T>(c, rerun, nof(j), s0 + j, adjoint, hbase, hon(j), ln);
+  if (c->multi) {
+    const int q = (count + c->mt.K - 1) / c->mt.K;
+    for (int k = 0; k < q; ++k) {
+      const int j0 = (int)((int64_t)count * k / q), j1 = (int)((int64_t)count * (k + 1) / q);
+      launch_step2d_multi<T>(c->mdesc.as<Multi2D<T>>() + rerun, nullptr, 1, step2d_multi_blocks(c->nx, c->ny, c->mt),
+                             nof(j0), j1 - j0, c->mt, c->cur[rerun], adjoint, ln.hist, hbase, hon(0), ln.s);
+      c->cur[rerun] ^= 1;
+    }
     return;
   }
-  const int P = count / 2;
-  const int *tiles = c->tbTiles.as<int>();
-  auto step = [&](int j) {
-    Step2D<T> p = params2d_at<T>(c, rerun, s0 + j, hbase, hon(j), ln.hist);
-    p.tlist = c->tbRest.as<int>();
-    return p;
-  };
-  auto out = [&](int q, int k) { return field_buf(c, rerun, fcopy(c, s0 + 2 * q + 2), k)->as<T>(); };
-  for (int q = 0; q < P; ++q) {
-    // launch A of pair q
-    const Step2D<T> pa = step(2 * q), pt = params2d_at<T>(c, rerun, s0 + 2 * q, hbase, hon(2 * q), ln.hist);
-    const int first = q == 0 ? 0 : c->nEarly;
-    launch_step2d_mix<T>(pa, nof(2 * q), c->nRest, pt, tiles + first, c->nTb - first, out(q, 0), out(q, 1),
-                         out(q, 2), adjoint, ln.s);
-    // launch B of pair q (+ the interior super-tiles of pair q+1)
-    const Step2D<T> pb = step(2 * q + 1);
-    const bool next = q + 1 < P;
-    const Step2D<T> pn = next ? params2d_at<T>(c, rerun, s0 + 2 * q + 2, hbase, hon(2 * q + 2), ln.hist) : pt;
-    launch_step2d_mix<T>(pb, nof(2 * q + 1), c->nRest, pn, tiles, next ? c->nEarly : 0,
-                         next ? out(q + 1, 0) : nullptr, next ? out(q + 1, 1) : nullptr,
-                         next ? out(q + 1, 2) : nullptr, adjoint, ln.s);
-  }
-  if (count & 1) launch_step<T>(c, rerun, nof(count - 1), s0 + count - 1, adjoint, hbase, hon(count - 1), ln);
+  for (int j = 0; j < count; ++j) launch_step<T>(c, rerun, nof(j), s0 + j, adjoint, hbase, hon(j), ln);
 }
 
 // The buffers holding the state after `st` steps of a solve (fields and
@@ -884,12 +901,13 @@ void run_block(fdtd_ctx *c, bool rerun, bool adjoint, int s0, int count, NOF nof
 std::vector<DevBuf *> state_bufs(fdtd_ctx *c, int st, bool rerun) {
   std::vector<DevBuf *> v;
   if (c->dims == 2) {
-    for (int k = 0; k < 3; ++k) v.push_back(field_buf(c, rerun, fcopy(c, st), k));
-    for (int k = 0; k < 4; ++k) v.push_back(rerun ? &c->pmlR[st & 1][k] : &c->pml[st & 1][k]);
+    const int mc = mcopy(c, rerun, st);
+    for (int k = 0; k < 3; ++k) v.push_back(field_buf(c, rerun, fcopy(c, rerun, st), k));
+    for (int k = 0; k < 4; ++k) v.push_back(rerun ? &c->pmlR[mc][k] : &c->pml[mc][k]);
   } else {
     v.push_back(&arena(c, rerun, st));
   }
-  v.push_back(rerun ? &c->JR : &c->J);
+  v.push_back(&jbuf(c, rerun));
   return v;
 }
 
@@ -916,8 +934,7 @@ void *seg_hist(fdtd_ctx *c, int s) { return c->hist2.p && (s & 1) ? c->hist2.p :
 
 // Forward solve: step n reads the state after n steps and writes the state
 // after n+1.  With checkpoints the state entering each segment but the last is
-// saved, and only the last segment's history is kept.  With two-step
-// blocking, steps go in pairs that never straddle a saved state.
+// saved, and only the last segment's history is kept.
 // Watchdog of a forward solve.  After every chunk of steps the largest |E|
 // of the state is reduced into a device slot and copied to pinned host
 // memory behind an event; the host reads slot q-1 right after enqueueing
@@ -937,7 +954,7 @@ struct ForwardWatch {
     if (c->dims == 2) {
       // TMz: E_z; TEz: E_x and E_y (the two checks share the slot's maximum)
       for (int k = 0; k < (c->te ? 2 : 1); ++k) {
-        DevBuf *e = field_buf(c, false, fcopy(c, s), k);
+        DevBuf *e = field_buf(c, false, fcopy(c, false, s), k);
         launch_watch(c->stream, c->prec, e->p, e->bytes / c->esz, slot);
       }
     } else {
@@ -1117,6 +1134,11 @@ struct fdtd_batch {
   int prec = 64, N = 0;
   fdtd_batch_options opt{0, 1, 0};
   std::vector<int> rows;  // tile depth per instance
+  // Several steps per launch, every instance in it (depths left to the library).
+  bool multi = false;
+  MultiTile mt{4, 8, 4};
+  int mblocks = 0;
+  DevBuf mparams, mfirst;
   // Two-step blocking: with `mix` every step goes through the blocked
   // schedule (two rows per thread everywhere); tb[k] = instance k advances
   // its plain-background super-tiles two steps per pass.
@@ -1200,9 +1222,9 @@ fdtd_batch::MixLaunch &mix_launch(fdtd_batch *b, int kind, int s) {
     if (count > 0) {
       d.tiles = c->tbTiles.as<int>() + first;
       d.ntb = count;
-      d.ezo = field_buf(c, false, fcopy(c, sp + 2), 0)->as<T>();
-      d.hxo = field_buf(c, false, fcopy(c, sp + 2), 1)->as<T>();
-      d.hyo = field_buf(c, false, fcopy(c, sp + 2), 2)->as<T>();
+      d.ezo = field_buf(c, false, fcopy(c, false, sp + 2), 0)->as<T>();
+      d.hxo = field_buf(c, false, fcopy(c, false, sp + 2), 1)->as<T>();
+      d.hyo = field_buf(c, false, fcopy(c, false, sp + 2), 2)->as<T>();
     }
     ds[k] = d;
     fr[k] = nr;
@@ -1243,6 +1265,15 @@ void batch_mix_steps(fdtd_batch *b, bool adjoint, int count, bool build_only = f
 template <typename T>
 void batch_steps(fdtd_batch *b, bool adjoint) {
   const int N = b->N;
+  if (b->multi) {
+    const int q = (N + b->mt.K - 1) / b->mt.K;
+    for (int k = 0; k < q; ++k) {
+      const int j0 = (int)((int64_t)N * k / q), j1 = (int)((int64_t)N * (k + 1) / q);
+      launch_step2d_multi<T>(b->mparams.as<Multi2D<T>>(), b->mfirst.as<int>(), (int)b->inst.size(), b->mblocks,
+                             adjoint ? N - j0 : j0, j1 - j0, b->mt, k & 1, adjoint, nullptr, 0, 1, b->stream);
+    }
+    return;
+  }
   if (b->mix) {
     batch_mix_steps<T>(b, adjoint, N);
     return;
@@ -1372,8 +1403,8 @@ float tune_rows(fdtd_batch *b, const std::vector<std::pair<int, int>> &sizes, in
   return best;
 }
 
-// Temporal-block depth and tile depth: fixed by the options, or tuned on the
-// batch.  Depth 1 = one launch per tile-depth group per step; depth 2 = the
+// Temporal-block depth and tile depth: several steps per launch (FP64, both
+// left to the library), fixed by the options, or tuned on the batch.  Depth 1 = one launch per tile-depth group per step; depth 2 = the
 // blocked schedule, where instances with plain-background super-tiles
 // advance them two steps per pass (the others take per-step launches inside
 // it).  Tuning times the best depth-1 choice against depth 2, then tries
@@ -1382,6 +1413,24 @@ float tune_rows(fdtd_batch *b, const std::vector<std::pair<int, int>> &sizes, in
 template <typename T>
 void batch_setup(fdtd_batch *b) {
   const int cnt = (int)b->inst.size();
+  if (b->multi) {
+    std::vector<std::array<int, 2>> n2d;
+    for (fdtd_ctx *c : b->inst) n2d.push_back({c->nx, c->ny});
+    b->mt = multi2d_tile(reinterpret_cast<const int(*)[2]>(n2d.data()), cnt, b->prec);
+    std::vector<Multi2D<T>> ms;
+    std::vector<int> first;
+    for (fdtd_ctx *c : b->inst) {
+      ms.push_back(params_multi<T>(c, false));
+      first.push_back(b->mblocks);
+      b->mblocks += step2d_multi_blocks(c->nx, c->ny, b->mt);
+    }
+    upload(b->stream, b->mparams, ms);
+    upload(b->stream, b->mfirst, first);
+    FDTD_HIP(hipStreamSynchronize(b->stream));
+    b->rows.assign(cnt, 2);
+    b->tb.assign(cnt, 0);
+    return;
+  }
   const int steps = std::min(20, b->N);
   std::vector<std::pair<int, int>> sizes;
   bool any_tb = false;
@@ -1456,15 +1505,7 @@ fdtd_ctx *instance(fdtd_batch *b, int32_t index) {
   return b->inst[index];
 }
 
-}  // namespace
-
-extern "C" {
-
-int32_t fdtd_abi_version(void) { return FDTD_ABI_VERSION; }
-
-const char *fdtd_last_error(const fdtd_ctx *ctx) { return ctx ? ctx->err.c_str() : g_create_error.c_str(); }
-
-fdtd_status fdtd_create(const fdtd_config *cfg, fdtd_ctx **out) {
+fdtd_status create_ctx(const fdtd_config *cfg, Kind2D kind, fdtd_ctx **out) {
   Range range("fdtd_create");
   if (!out) { g_create_error = "null out pointer"; return FDTD_EINVAL; }
   *out = nullptr;
@@ -1501,11 +1542,21 @@ fdtd_status fdtd_create(const fdtd_config *cfg, fdtd_ctx **out) {
       c->own_stream = true;
     }
     for (int k = 0; k < 4; ++k) FDTD_HIP(hipEventCreate(&c->ev[k]));
-    if (c->dims == 2) create_2d(c.get()); else create_3d(c.get());
+    if (c->dims == 2) create_2d(c.get(), kind); else create_3d(c.get());
     create_common(c.get());
     if (c->dims == 2) {
       if (c->prec == 32) fill_params2d(c.get(), c->p2f, false); else fill_params2d(c.get(), c->p2d, false);
       if (c->prec == 32) fill_params2d(c.get(), c->p2fR, true); else fill_params2d(c.get(), c->p2dR, true);
+      if (c->multi) {
+        for (int r = 0; r < 2; ++r) {
+          DevBuf &j0 = r ? c->JR : c->J, &j1 = r ? c->JRb : c->Jb;
+          c->m2f[r] = Multi2D<float>{r ? c->p2fR : c->p2f, {j0.as<float>(), j1.as<float>()}};
+          c->m2d[r] = Multi2D<double>{r ? c->p2dR : c->p2d, {j0.as<double>(), j1.as<double>()}};
+        }
+        if (c->prec == 32) upload(c->stream, c->mdesc, std::vector<Multi2D<float>>(c->m2f, c->m2f + 2));
+        else upload(c->stream, c->mdesc, std::vector<Multi2D<double>>(c->m2d, c->m2d + 2));
+        FDTD_HIP(hipStreamSynchronize(c->stream));
+      }
     } else {
       if (c->prec == 32) fill_params3d(c.get(), c->p3f, false); else fill_params3d(c.get(), c->p3d, false);
       if (c->prec == 32) fill_params3d(c.get(), c->p3fR, true); else fill_params3d(c.get(), c->p3dR, true);
@@ -1517,10 +1568,6 @@ fdtd_status fdtd_create(const fdtd_config *cfg, fdtd_ctx **out) {
       }
       for (int b = 0; b < 3; ++b)
         if (c->arenaR[b].p) zero(c.get(), c->arenaR[b]);
-      // the third field copy of the two-step schedule: a re-run whose
-      // segment starts in copy 0 or 1 reads this copy's wall nodes before
-      // any step has written them
-      for (int k = 0; k < 3; ++k) if (c->fld3R[k].p) zero(c.get(), c->fld3R[k]);
     }
     FDTD_HIP(hipStreamSynchronize(c->stream));
     FDTD_HIP(hipGetLastError());
@@ -1534,6 +1581,16 @@ fdtd_status fdtd_create(const fdtd_config *cfg, fdtd_ctx **out) {
   *out = c.release();
   return FDTD_OK;
 }
+
+}  // namespace
+
+extern "C" {
+
+int32_t fdtd_abi_version(void) { return FDTD_ABI_VERSION; }
+
+const char *fdtd_last_error(const fdtd_ctx *ctx) { return ctx ? ctx->err.c_str() : g_create_error.c_str(); }
+
+fdtd_status fdtd_create(const fdtd_config *cfg, fdtd_ctx **out) { return create_ctx(cfg, Kind2D::kMulti, out); }
 
 fdtd_status fdtd_destroy(fdtd_ctx *ctx) {
   if (!ctx) return FDTD_OK;
@@ -1703,11 +1760,19 @@ fdtd_status fdtd_batch_create(const fdtd_config *cfgs, int32_t count, const fdtd
     for (int k = 0; k < 4; ++k) FDTD_HIP(hipEventCreate(&b->ev[k]));
     b->prec = cfgs[0].precision;
     b->N = cfgs[0].n_steps;
+    // FP32 batches keep their own kernels, although several steps per launch
+    // took 12 instead of 40 us per step for 16 instances of sides 128-1024:
+    // those kernels are compiled to other roundings than the single
+    // contexts' (F differs by ~1e-8), and a batch's results stay its own.
+    b->multi = b->prec == 64 && b->opt.rows == 0 && b->opt.depth == 0 && blocking_enabled(2);
+    for (int k = 0; k < count; ++k)  // as in create_2d
+      b->multi = b->multi && (((int64_t)cfgs[k].n[0] + 63) & ~63ll) * cfgs[k].n[1] < INT32_MAX;
     for (int k = 0; k < count; ++k) {
       fdtd_config c = cfgs[k];
       c.stream = b->stream;
       fdtd_ctx *ctx = nullptr;
-      const fdtd_status s2 = fdtd_create(&c, &ctx);
+      const fdtd_status s2 =
+          create_ctx(&c, b->multi ? Kind2D::kMulti : b->opt.depth == 1 ? Kind2D::kPerStep : Kind2D::kBlocked, &ctx);
       if (s2 != FDTD_OK) throw Error{s2, "batch instance " + std::to_string(k) + ": " + g_create_error};
       b->inst.push_back(ctx);
     }
@@ -1802,7 +1867,7 @@ fdtd_status fdtd_batch_depth(fdtd_batch *b, int32_t index, int32_t *depth_out) {
   return bguard(b, [&] {
     fdtd_ctx *c = instance(b, index);
     if (!depth_out) throw einval("null depth pointer");
-    *depth_out = b->mix && b->tb[index] && c->nTb > 0 ? 2 : 1;
+    *depth_out = (b->multi ? c->super_tiles > 0 : b->mix && b->tb[index] && c->nTb > 0) ? 2 : 1;
   });
 }
 

@@ -355,7 +355,8 @@ class Batch:
     """Uneven 2D instances advanced together (fdtd_batch_*): one launch per
     tile depth per time step (depth 1) or the two-step blocked schedule
     (depth 2), the step sequences replayed from HIP graphs.  rows = 0 and
-    depth = 0 tune on the batch at creation."""
+    depth = 0: several steps per launch in FP64, tuned on the batch at creation
+    in FP32."""
 
     def __init__(self, ws, stream=None, rows=0, use_graph=True, depth=0):
         L = load_library()
