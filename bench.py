@@ -39,7 +39,7 @@ HBM_PEAK_GBS = 8000.0
 SRC_2D = ["paper_2203_01462_amd/csrc/fdtd_2d_multi.hip", "paper_2203_01462_amd/csrc/fdtd_api.hip"]
 SRC_BATCH = ["paper_2203_01462_amd/csrc/fdtd_2d.hip", "paper_2203_01462_amd/csrc/fdtd_api.hip"]
 SRC_3D = ["paper_2203_01462_amd/csrc/fdtd_3d.hip", "paper_2203_01462_amd/csrc/fdtd_api.hip"]
-SRC_TE = ["paper_2203_01462_amd/csrc/fdtd_te.hip", "paper_2203_01462_amd/csrc/fdtd_api.hip"]
+SRC_TE = ["paper_2203_01462_amd/csrc/fdtd_te_multi.hip", "paper_2203_01462_amd/csrc/fdtd_api.hip"]
 MEASURED_TRAFFIC = {}
 
 
@@ -60,7 +60,7 @@ def measured_traffic(name):
     # the counters were taken with the default schedules (2D: several steps
     # per launch; 3D: one)
     tb = os.environ.get("FDTD_TEMPORAL_BLOCKING", "")
-    if (tb == "0" and rec["sources"] in (SRC_2D, SRC_BATCH)) or (tb == "1" and rec["sources"] is SRC_3D):
+    if (tb == "0" and rec["sources"] in (SRC_2D, SRC_BATCH, SRC_TE)) or (tb == "1" and rec["sources"] is SRC_3D):
         return None, None
     try:
         h = sources_sha(rec["sources"])
@@ -369,7 +369,7 @@ def main():
                 # counter-measured HBM bytes per step over the same event time
                 "measured_gbs": round(traffic / step_s / 1e9, 1) if traffic else None,
                 "measured_frac": round(traffic / step_s / 1e9 / HBM_PEAK_GBS, 4) if traffic else None,
-                "kernel": ("step_te_fwd / step_te_adj (one launch per time step)" if W.is_te(base)
+                "kernel": ("step_te_multi (several time steps per launch)" if W.is_te(base)
                            else "step2d_multi (several time steps per launch)" if base["dims"] == 2
                            else "step3d_general_fwd (forward) or step3d_general x3 (adjoint) + step3d_plain"
                                 " (one time step)"),

@@ -147,6 +147,13 @@ void launch_step2d_multi(const Multi2D<T> *ms, const int *first, int ninst, int 
                          const MultiTile &g, int rd, bool adjoint, void *hist, int hist_base, int hist_on,
                          hipStream_t s);
 
+// The same for one 2D TEz context (fdtd_te_multi.hip; arrays as in
+// launch_step_te).
+MultiTile multi_te_tile(int nx, int ny, int precision);
+template <typename T>
+void launch_step_te_multi(const Multi2D<T> *m, int nx, int ny, int n0, int steps, const MultiTile &g, int rd,
+                          bool adjoint, void *hist, int hist_base, int hist_on, hipStream_t s);
+
 // One time step of several instances (device array `ps` of their parameters,
 // `first[k]` = first workgroup of instance k, blocks of each instance padded
 // to a multiple of 8; `nblocks` = total), all with the same tile depth.

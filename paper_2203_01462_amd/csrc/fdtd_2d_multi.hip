@@ -37,42 +37,11 @@
 // hold the identity (b = 1, a = 0, 1/kappa = 1) and the memories are zero, so
 // a graded difference needs no per-lane choice.
 #include <algorithm>
-#include <utility>
 
-#include "fdtd_2d.hpp"
+#include "fdtd_multi.hpp"
 
 namespace fdtd {
 namespace {
-
-constexpr int MX = 64;          // columns of a region: one wavefront
-constexpr int MKMAX = 12;       // most steps per launch
-constexpr int MWMAX = 16;       // most wavefronts per workgroup
-
-template <typename T>
-using cptr = const __attribute__((address_space(4))) T *;
-template <typename T>
-using gptr = __attribute__((address_space(1))) T *;
-
-__device__ __forceinline__ bool pml_e(int i, int n, int P) { return P > 0 && (i < P || i > n - 1 - P); }
-__device__ __forceinline__ bool pml_h(int i, int n, int P) { return P > 0 && (i < P || i >= n - 1 - P); }
-
-// The value of lane - 1 (wave_shr:1) / lane + 1 (wave_shl:1); 0 in the lane
-// without one, which only feeds nodes outside the exact middle.
-template <int CTRL>
-__device__ __forceinline__ float lane_shift(float v) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
-}
-template <int CTRL>
-__device__ __forceinline__ double lane_shift(double v) {
-  const long long b = __double_as_longlong(v);
-  const unsigned lo = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(b & 0xffffffffll), CTRL, 0xf, 0xf, true);
-  const unsigned hi = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xf, 0xf, true);
-  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
-}
-template <typename T>
-__device__ __forceinline__ T lane_left(T v) { return lane_shift<0x138>(v); }
-template <typename T>
-__device__ __forceinline__ T lane_right(T v) { return lane_shift<0x130>(v); }
 
 // LDS of a workgroup: the exchanged rows [2][waves][2][64] and, where the
 // region meets an injection line, the incident values of the launch's steps:
@@ -82,14 +51,6 @@ struct MultiLds {
   T x[2 * MWMAX * 2 * MX];
   T ei[MKMAX * 64];
   T ab[MKMAX * 4];
-};
-
-// What a launch does: `steps` steps from step number n0 on (ascending, or
-// descending in the adjoint), copy rd read and copy rd ^ 1 written.
-struct MultiStep {
-  int n0, steps, rd;
-  void *hist;  // history buffer (null: the instance's own, every step kept)
-  int hist_base, hist_on;
 };
 
 // One region with origin (x0, y0); its nodes [K, 64 - K) x [K, R nw - K) are
@@ -464,11 +425,11 @@ __device__ __forceinline__ void multi_body(cptr<Multi2D<T>> m, const MultiStep s
     }
     if constexpr (PX) {
       T *q0 = m->s.pex[wr], *q1 = m->s.phy[wr];
-      if (ownx && pml_e(i, nx, P))
+      if (ownx && pml_e2(i, nx, P))
 #pragma unroll
         for (int r = 0; r < R; ++r)
           if (owny(r)) ((gptr<T>)(q0 + (int64_t)(jb + r) * pitch))[i] = pex[r];
-      if (ownx && pml_h(i, nx, P))
+      if (ownx && pml_h2(i, nx, P))
 #pragma unroll
         for (int r = 0; r < R; ++r)
           if (owny(r)) ((gptr<T>)(q1 + (int64_t)(jb + r) * pitch))[i] = phy[r];
@@ -479,8 +440,8 @@ __device__ __forceinline__ void multi_body(cptr<Multi2D<T>> m, const MultiStep s
 #pragma unroll
         for (int r = 0; r < R; ++r) {
           const int j = jb + r;
-          if (owny(r) && pml_e(j, ny, P)) ((gptr<T>)(q0 + (int64_t)j * pitch))[i] = pey[r];
-          if (owny(r) && pml_h(j, ny, P)) ((gptr<T>)(q1 + (int64_t)j * pitch))[i] = phx[r + 1];
+          if (owny(r) && pml_e2(j, ny, P)) ((gptr<T>)(q0 + (int64_t)j * pitch))[i] = pey[r];
+          if (owny(r) && pml_h2(j, ny, P)) ((gptr<T>)(q1 + (int64_t)j * pitch))[i] = phx[r + 1];
         }
       }
     }
@@ -553,10 +514,7 @@ __global__ void __launch_bounds__(64 * MWMAX)
 
 }  // namespace
 
-int step2d_multi_blocks(int nx, int ny, const MultiTile &g) {
-  const int W = MX - 2 * g.K, H = g.R * g.nw - 2 * g.K;
-  return ((nx + W - 1) / W) * ((ny + H - 1) / H);
-}
+int step2d_multi_blocks(int nx, int ny, const MultiTile &g) { return multi_regions(nx, ny, g); }
 
 // Regions by size.  While one round of the 256 CUs holds them all, a launch
 // takes one region's time: the flattest region that still fits wins (fewer

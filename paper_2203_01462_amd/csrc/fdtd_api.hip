@@ -43,8 +43,8 @@ struct fdtd_ctx {
   // checkpointed adjoint: a second state (both copies and J) for re-running
   // forward segments, and the snapshots [nseg-1][state copy + J]
   DevBuf fldR[2][6], pmlR[2][12], arenaR[3], JR, snap;
-  // 2D TMz, several steps per launch (fdtd_2d_multi.hip): the second copy of
-  // the Drude current, the regions and the copy that holds the state now
+  // 2D, several steps per launch (fdtd_2d_multi.hip, fdtd_te_multi.hip): the
+  // second copy of the Drude current, the regions and the copy that holds the state now
   // (main and re-run; the launches alternate between the copies)
   bool multi = false;
   DevBuf Jb, JRb;
@@ -101,7 +101,7 @@ namespace {
 
 thread_local std::string g_create_error;  // per thread: creates may run on several threads
 
-// How a 2D TMz context steps: several steps per launch (single contexts, and
+// How a 2D context steps: several steps per launch (single contexts, and
 // FP64 batches that leave the tile and block depths to the library), one step
 // per launch, or a batch's two-step blocked schedule.
 enum class Kind2D { kMulti, kPerStep, kBlocked };
@@ -314,10 +314,10 @@ void create_2d(fdtd_ctx *c, Kind2D kind) {
                    : tb2d_plan(c->nx, c->ny, P, -8, -8, -8, -8, dbox, gbox);
   c->super_tiles = (int)pl.tb.size();
   // (the several-step kernel indexes a field with 32 bits)
-  c->multi = !c->te && kind == Kind2D::kMulti && blocking_enabled(2) && (int64_t)c->pitch * c->ny < INT32_MAX;
+  c->multi = kind == Kind2D::kMulti && blocking_enabled(2) && (int64_t)c->pitch * c->ny < INT32_MAX;
   if (c->multi) {
     const int n2d[1][2] = {{c->nx, c->ny}};
-    c->mt = multi2d_tile(n2d, 1, c->prec);
+    c->mt = c->te ? multi_te_tile(c->nx, c->ny, c->prec) : multi2d_tile(n2d, 1, c->prec);
   }
   if (!pl.tb.empty() && kind == Kind2D::kBlocked && blocking_enabled(2) && !c->te) {
     // the interior super-tiles run one launch early (beside the rest tiles'
@@ -844,7 +844,7 @@ Multi2D<double> &params_multi<double>(fdtd_ctx *c, bool rerun) { return c->m2d[r
 
 // `count` consecutive time steps of a solve, the first one the (s0+1)-th:
 // step j has step number nof(j), history base hbase and history flag hon(j).
-// With several steps per launch (2D TMz) the block is the fewest launches,
+// With several steps per launch (2D) the block is the fewest launches,
 // their step counts as even as they go (callers' blocks never straddle a saved
 // state, so the history flag holds for a whole block).
 //
@@ -887,8 +887,13 @@ void run_block(fdtd_ctx *c, bool rerun, bool adjoint, int s0, int count, NOF nof
     const int q = (count + c->mt.K - 1) / c->mt.K;
     for (int k = 0; k < q; ++k) {
       const int j0 = (int)((int64_t)count * k / q), j1 = (int)((int64_t)count * (k + 1) / q);
-      launch_step2d_multi<T>(c->mdesc.as<Multi2D<T>>() + rerun, nullptr, 1, step2d_multi_blocks(c->nx, c->ny, c->mt),
-                             nof(j0), j1 - j0, c->mt, c->cur[rerun], adjoint, ln.hist, hbase, hon(0), ln.s);
+      const Multi2D<T> *m = c->mdesc.as<Multi2D<T>>() + rerun;
+      if (c->te)
+        launch_step_te_multi<T>(m, c->nx, c->ny, nof(j0), j1 - j0, c->mt, c->cur[rerun], adjoint, ln.hist, hbase,
+                                hon(0), ln.s);
+      else
+        launch_step2d_multi<T>(m, nullptr, 1, step2d_multi_blocks(c->nx, c->ny, c->mt), nof(j0), j1 - j0, c->mt,
+                               c->cur[rerun], adjoint, ln.hist, hbase, hon(0), ln.s);
       c->cur[rerun] ^= 1;
     }
     return;

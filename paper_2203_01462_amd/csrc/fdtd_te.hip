@@ -25,9 +25,9 @@
 // loaded before the current row's arithmetic.  Blocks whose nodes reach the
 // design or gap box take one row per wavefront and a body with the design
 // and gap code; all other blocks a body without it.  Every array a halo
-// reads has a read and a write copy.  This polarization's workloads are small (the
-// paper's 2D designs), so the step is a plain per-step kernel without
-// temporal blocking.
+// reads has a read and a write copy.  Contexts take several steps per launch
+// (fdtd_te_multi.hip) unless that is switched off or a field exceeds 32-bit
+// indices; this kernel remains for those.
 
 // Design layout (per edge): the design box of dnx x dny cells holds its E_x
 // edges [dny+1][dnx] (density indices 0 .. ndx-1) followed by its E_y edges

@@ -1,11 +1,11 @@
-"""Several time steps per launch (2D TMz) against the per-step kernels at the
-sizes where the regions can go wrong: grids smaller than a region, one node
+"""Several time steps per launch (2D TMz and TEz) against the per-step kernels at
+the sizes where the regions can go wrong: grids smaller than a region, one node
 around the multiples of the stored widths of each region shape, no absorber,
 step counts that leave a shorter last launch, boxes at the edge of what is
 allowed, a gap too large for the staged adjoint source.  Both paths start from
-a random state with the plane wave on.  FP64: F, the final state and the
-gradient to the last bit (both kernels write out the roundings of a node's
-update).  FP32: 1e-4 on F and the state, 1e-3 on the gradient, the bars of
+a random state with the plane wave on.  TMz in FP64: F, the final state and
+the gradient to the last bit (both kernels write out the roundings of a node's
+update); TEz in FP64 to 1e-11, the bar against the oracle.  FP32: 1e-4 on F and the state, 1e-3 on the gradient, the bars of
 this precision against the oracle."""
 import os
 
@@ -76,3 +76,37 @@ def test_multi_step_matches_per_step(gpu, prec, nx, ny, pml, box, gap, steps, ck
         assert abs(F1 - F0) <= 1e-4 * F0
         assert np.linalg.norm(s1 - s0) <= 1e-4 * np.linalg.norm(s0)
         assert np.linalg.norm(g1 - g0) <= 1e-3 * np.linalg.norm(g0)
+
+
+# (nx, ny, pml, design cells, gap cells, steps)
+TE_CASES = [
+    (30, 32, 3, 6, 2, 23),        # smaller than one region
+    (44, 24, 0, 5, 1, 21),        # one stored width, walls without an absorber
+    (45, 25, 2, 4, 3, 20),        # one node more
+    (89, 133, 6, 30, 20, 31),     # a gap of 840 edges (adjoint source not staged)
+    (385, 400, 12, 90, 3, 17),    # 48 x 16 stored nodes on several rounds
+    (901, 1000, 20, 300, 7, 13),  # the large-grid regions
+]
+
+
+@pytest.mark.parametrize("prec", [64, 32])
+@pytest.mark.parametrize("nx,ny,pml,box,gap,steps", TE_CASES)
+def test_te_multi_step_matches_per_step(gpu, prec, nx, ny, pml, box, gap, steps):
+    m = 3
+    lo = ((nx - box) // 2, pml + m + 1, 0)  # its lower edges next to the injection line
+    glo = (nx // 2, lo[1] + box // 2, 0) if gap < box else lo
+    glo = tuple(min(a, n - 2 - pml - m - gap - 1) for a, n in zip(glo[:2], (nx, ny))) + (0,)
+    w = W.tiny_te(precision=prec, n=(nx, ny, 1), pml_cells=pml, tfsf_margin=m, n_steps=steps, t0_over_tau=0.2,
+                  design_lo=lo, design_n=(box, box, 1), gap_lo=glo, gap_n=(gap, gap, 1), pml_kappa_max=2.0)
+    rho = W.seeded_rho(w, 5)
+    state = np.random.default_rng(3).standard_normal((5, 1, ny, nx))
+    state[2] *= 2.6e-3
+    state[3:] *= 1e5
+    say(f"[multi2d] TEz {nx}x{ny} fp{prec} steps={steps}")
+    F0, s0, g0 = solve(gpu, w, rho, state, True, 0)
+    F1, s1, g1 = solve(gpu, w, rho, state, False, 0)
+    assert F0 > 0 and np.abs(g0).max() > 0
+    tf, tg = (1e-11, 1e-11) if prec == 64 else (1e-4, 1e-3)
+    assert abs(F1 - F0) <= tf * abs(F0)
+    assert np.linalg.norm(s1 - s0) <= tf * np.linalg.norm(s0)
+    assert np.linalg.norm(g1 - g0) <= tg * np.linalg.norm(g0)
