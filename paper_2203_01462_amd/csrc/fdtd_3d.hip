@@ -17,7 +17,8 @@
 // step's values, which the ping-pong copies keep intact.  A tile-plane is
 // "plain" when its whole reach is background dielectric; all others
 // (absorber, walls, injection faces, Drude design edges, gap) are "general".
-// One step is the general update over three host-built lists of
+// Small grids take one launch a step (step3d_whole), all tile-planes in the
+// general update.  Otherwise a step is the general update over three host-built lists of
 // tile-chunks (one absorber axis or none; several axes; design and gap) --
 // one launch of step3d_general_fwd in the FP32 forward (design box clear of
 // the absorber), else three launches of step3d_general, the multi-axis one
@@ -193,8 +194,22 @@ __device__ __forceinline__ T grc(T v, T m, const Ax<T> &x, T &mn) {
   }
 }
 
-template <typename T, bool ADJ, bool DES, int AX>
-__device__ __forceinline__ void general_chunk(const Step3D<T> &p, const int n, const Tile &tl) {
+// The parameters (in the kernel's argument segment) read again at this point, as
+// scalar loads, instead of being held - and spilled to vector registers - across
+// the march.  FP64 80^3: 32.3 / 38.2 -> 28.8 / 29.2 us per forward / adjoint step
+// (552 -> 145 spilled scalars); FP32 holds them (160^3 46.8 / 54.5 against
+// 51.1 / 54.2).
+template <typename T>
+__device__ __forceinline__ const Step3D<T> &again(const Step3D<T> *pp) {
+  cptr<Step3D<T>> c = (cptr<Step3D<T>>)pp;
+  asm volatile("" : "+s"(c));
+  return *(const Step3D<T> *)c;
+}
+
+// ALL: every plane takes this update, plain ones too.
+template <typename T, bool ADJ, bool DES, int AX, bool ALL = false>
+__device__ __forceinline__ void general_chunk(const Step3D<T> &pp, const int n, const Tile &tl) {
+  const Step3D<T> &p = pp;
   const int nx = p.n[0], ny = p.n[1], nz = p.n[2], P = p.P;
   auto gx = [](T v, T m, const Ax<T> &x, T &mn) { return grc<(AX & 1) != 0>(v, m, x, mn); };
   auto gy = [](T v, T m, const Ax<T> &x, T &mn) { return grc<(AX & 2) != 0>(v, m, x, mn); };
@@ -262,6 +277,7 @@ __device__ __forceinline__ void general_chunk(const Step3D<T> &p, const int n, c
 
   auto plane = [&](auto store_tag, const int k) {
     constexpr bool STORE = decltype(store_tag)::value;
+    const Step3D<T> &p = ALL && sizeof(T) == 8 ? again(&pp) : pp;
     if (k < 0) {  // below the grid: no H
       hxp = hyp = T(0);
       return;
@@ -580,7 +596,7 @@ __device__ __forceinline__ void general_chunk(const Step3D<T> &p, const int n, c
 
   bool have = false;  // carried values hold plane k-1
   for (int k = tl.kb; k < tl.ke; ++k) {
-    if (plane_plain(p, tl, k)) {
+    if (!ALL && plane_plain(p, tl, k)) {
       have = false;
       continue;
     }
@@ -651,6 +667,34 @@ step3d_general_fwd(const Step3D<float> p, const int n, const int *__restrict__ l
   if (b < p.gS) general_body<float, false, false, 8>(p, n, code);
   else if (b < p.gS + p.gM) general_body<float, false, false, 7>(p, n, code);
   else general_body<float, false, true, 0>(p, n, code);
+}
+
+// One launch a step, for grids whose step is bound by latency: tile-chunks of
+// every kind (whole3d_plan) with a uniform branch to their bodies.  Plain planes
+// take the body without absorber axes, so nothing waits for another launch.  The
+// rarest body sets the registers (FP64 adjoint 256, FP32 forward 131); holding
+// the kernel to three or four wavefronts a SIMD spills the others' (FP64 80^3
+// 28.8 / 29.2 us -> 29.5 / 61.5 and 51 / 83).
+template <typename T, bool ADJ, bool DABS>
+__global__ void __launch_bounds__(NT) step3d_whole(const Step3D<T> arg, const int n,
+                                                        const int *__restrict__ list) {
+  const Step3D<T> &p = *(const Step3D<T> *)(cptr<Step3D<T>>)__builtin_amdgcn_kernarg_segment_ptr();
+  const int code = ((cptr<int>)list)[blockIdx.x];
+  if (code < 0) return;
+  const int c = code >> 3;
+  const int nbx = (p.n[0] + TX - 1) / TX, nby = (p.n[1] + TY - 1) / TY;
+  const int bx = c % nbx, by = (c / nbx) % nby, bz = c / (nbx * nby);
+  Tile tl = tile_xy(p, bx * TX, by * TY);
+  tl.kb = bz * p.kc;
+  tl.ke = min(tl.kb + p.kc, p.n[2]);
+  switch (code & 7) {
+    case 0: general_chunk<T, ADJ, false, 1, true>(p, n, tl); break;
+    case 1: general_chunk<T, ADJ, false, 2, true>(p, n, tl); break;
+    case 2: general_chunk<T, ADJ, false, 4, true>(p, n, tl); break;
+    case 3: general_chunk<T, ADJ, false, 0, true>(p, n, tl); break;
+    case 4: general_chunk<T, ADJ, false, 7, true>(p, n, tl); break;
+    default: general_chunk<T, ADJ, true, DABS ? 7 : 0, true>(p, n, tl);
+  }
 }
 
 // ---------------------------------------------------------------- plain
@@ -1069,6 +1113,45 @@ std::vector<int> gen3d_plan(const Step3D<T> &p, int &nS, int &nM, int &nD, int &
   return out;
 }
 
+// While both copies of the six fields fit in about twice the 256 MB cache behind
+// the L2s, a step is bound by its launches and their chains of planes, and one
+// launch wins; beyond, by the bytes, and the plain kernel's wider tiles win.  us per
+// forward / adjoint step, lists and plain launch against one launch:
+//   FP32  48^3 35 / 33 -> 11 / 10   80^3 46 / 45 -> 19 / 21   112^3 39 / 53 -> 27 / 32
+//        160^3 81 / 96 -> 47 / 55  200^3 142 / 162 -> 136 / 158  (256^3 254 / 276 -> 252 / 298)
+//   FP64  48^3 41 / 40 -> 14 / 15   80^3 64 / 63 -> 29 / 29   112^3 80 / 85 -> 58 / 57
+//        160^3 183 / 194 -> 161 / 169  (200^3 305 / 322 -> 312 / 332)
+// A chunk recomputes the H of the plane below it: four planes where that leaves
+// four workgroups a CU, else two for a shorter chain (FP32 48^3 15.5 / 13.7 with
+// four; 160^3 54 / 62 with two).
+template <typename T>
+std::vector<int> whole3d_plan(const Step3D<T> &p, int &kc, int &axD) {
+  const int nx = p.n[0], ny = p.n[1], nz = p.n[2];
+  if ((int64_t)nx * ny * nz * 12 * (int64_t)sizeof(T) > (int64_t)512 << 20) return {};
+  kc = (int64_t)((nx + TX - 1) / TX) * ((ny + TY - 1) / TY) * ((nz + 3) / 4) >= 1024 ? 4 : 2;
+  axD = 0;
+  const int nbx = (nx + TX - 1) / TX, nby = (ny + TY - 1) / TY, nbz = (nz + kc - 1) / kc;
+  std::vector<int> codes, group, work;
+  for (int bz = 0; bz < nbz; ++bz)
+    for (int by = 0; by < nby; ++by)
+      for (int bx = 0; bx < nbx; ++bx) {
+        Tile tl = tile_xy(p, bx * TX, by * TY);
+        tl.kb = bz * kc;
+        tl.ke = std::min(tl.kb + kc, nz);
+        int ax = tile_axes(p, tl);
+        for (int k = std::max(tl.kb - 1, 0); k < tl.ke; ++k) ax |= plane_axes(p, k);
+        int v = ax == 1 ? 0 : ax == 2 ? 1 : ax == 4 ? 2 : ax == 0 ? 3 : 4;
+        if (design_chunk(p, tl)) {
+          v = 5;
+          axD |= ax;
+        }
+        codes.push_back(8 * ((bz * nby + by) * nbx + bx) + v);
+        group.push_back(bz * ((nby + 3) / 4) + by / 4);
+        work.push_back(tl.ke - tl.kb + 1);
+      }
+  return xcd_order(codes, group, work);
+}
+
 template <typename T>
 std::vector<int> plan3d_super(const Step3D<T> &p, int so[3], int sn[3], std::vector<unsigned char> &flags) {
   const int n3[3] = {p.n[0], p.n[1], p.n[2]}, nx = n3[0], ny = n3[1], nz = n3[2], P = p.P;
@@ -1246,6 +1329,13 @@ void launch_step3d(const Step3D<T> &p, T *rd, T *wr, int n, bool adjoint, hipStr
   Step3D<T> q = p;  // copy 0 is read, copy 1 written
   q.A[0] = rd;
   q.A[1] = wr;
+  if (q.gW > 0) {
+    if (adjoint && q.gWD) hipLaunchKernelGGL((step3d_whole<T, true, true>), dim3(q.gW), dim3(NT), 0, s, q, n, q.wlist);
+    else if (adjoint) hipLaunchKernelGGL((step3d_whole<T, true, false>), dim3(q.gW), dim3(NT), 0, s, q, n, q.wlist);
+    else if (q.gWD) hipLaunchKernelGGL((step3d_whole<T, false, true>), dim3(q.gW), dim3(NT), 0, s, q, n, q.wlist);
+    else hipLaunchKernelGGL((step3d_whole<T, false, false>), dim3(q.gW), dim3(NT), 0, s, q, n, q.wlist);
+    return;
+  }
   // the general tile-chunks (one launch, or three by what they need), then
   // the plain ones, which read back the new H of a general plane below them
   if (adjoint) launch_general<T, true>(q, n, s, aux);
@@ -1282,6 +1372,8 @@ void plain3d_box(const Step3D<T> &p, int pb[6]) {
 
 template std::vector<int> gen3d_plan<float>(const Step3D<float> &, int &, int &, int &, int &);
 template std::vector<int> gen3d_plan<double>(const Step3D<double> &, int &, int &, int &, int &);
+template std::vector<int> whole3d_plan<float>(const Step3D<float> &, int &, int &);
+template std::vector<int> whole3d_plan<double>(const Step3D<double> &, int &, int &);
 template void plain3d_box<float>(const Step3D<float> &, int *);
 template void plain3d_box<double>(const Step3D<double> &, int *);
 template void launch_step3d<float>(const Step3D<float> &, float *, float *, int, bool, hipStream_t, const Aux3D &);

@@ -89,6 +89,11 @@ struct Step3D {
   // absorber axes the design chunks reach (0 or 7)
   const int *glist;
   int gS, gM, gD, gAxD;
+  // One launch a step (small grids): the list of all tile-chunks of kc planes
+  // (from whole3d_plan), its length and whether a design chunk meets the
+  // absorber; gW = 0: the lists above and the plain launch.
+  const int *wlist;
+  int gW, gWD, kc;
   int pb[6];  // bounding box of the plain tile-planes: origin x, y, z, extent x, y, z (from plain3d_box)
   // Two-step blocking of the plain background (see plan3d_super): the grid of
   // super-chunks (origin so, chunk counts sn), one flag byte per chunk
@@ -124,6 +129,13 @@ std::vector<int> plan3d_super(const Step3D<T> &p, int so[3], int sn[3], std::vec
 template <typename T>
 std::vector<int> gen3d_plan(const Step3D<T> &p, int &nS, int &nM, int &nD, int &axD);
 
+// Every tile-chunk of kc planes with the body it takes (code 8c + v: v = 0, 1, 2
+// one absorber axis, 3 none, 4 several, 5 design without, 6 design with
+// absorber), in the order of gen3d_plan; empty when the grid takes the lists
+// above.  axD: a design chunk meets the absorber.
+template <typename T>
+std::vector<int> whole3d_plan(const Step3D<T> &p, int &kc, int &axD);
+
 // Bounding box of the tile-planes that take the plain update (extent 0
 // when there are none); the plain launch covers only this box.
 template <typename T>
@@ -139,8 +151,8 @@ struct Aux3D {
   hipEvent_t fork, join;
 };
 
-// One time step: copy rd read, copy wr written (general launches, then the
-// plain launch, which skips the super-chunks when p.skip_super is set).
+// One time step: copy rd read, copy wr written (one launch with p.gW, else the
+// general launches, then the plain launch, which skips the super-chunks when p.skip_super is set).
 template <typename T>
 void launch_step3d(const Step3D<T> &p, T *rd, T *wr, int n, bool adjoint, hipStream_t s, const Aux3D &aux);
 
