@@ -13,6 +13,7 @@
 #include <map>
 #include <mutex>
 #include <string>
+#include <type_traits>
 
 #include "fdtd_internal.hpp"
 #include "fdtd_nn.h"
@@ -94,6 +95,41 @@ __device__ __forceinline__ void tile_out16(const f4 (&acc)[4], const uint16_t (&
       for (int s = 0; s < 4; ++s) a[o + (size_t)s * w] = b[s][j];
     }
   }
+}
+
+// Elements xs .. xs + 7 (xs >= 0) of a row of w elements at any address, zero beyond
+// the row: one 16-byte load (the type says 2-byte alignment) that starts early
+// enough to end inside the row (raw8), shifted down when it is used (cut8); rows
+// of less than 8 element by element.  row must be readable also where the caller
+// discards the result.
+__device__ __forceinline__ uint4 raw8(const uint16_t *row, int xs, int w) {
+  struct __attribute__((packed, aligned(2))) V {
+    uint32_t v[4];
+  };
+  if (w >= 8) {
+    const V v = *(const V *)(row + min(xs, w - 8));
+    return uint4{v.v[0], v.v[1], v.v[2], v.v[3]};
+  }
+  uint32_t e[8];
+#pragma unroll
+  for (int q = 0; q < 8; ++q) {
+    e[q] = row[min(xs + q, w - 1)];
+    if (xs + q >= w) e[q] = 0u;
+  }
+  return uint4{e[0] | (e[1] << 16), e[2] | (e[3] << 16), e[4] | (e[5] << 16), e[6] | (e[7] << 16)};
+}
+__device__ __forceinline__ uint4 cut8(uint4 v, int xs, int w, bool ok) {
+  const int past = w >= 8 ? min(max(xs - (w - 8), 0), 8) : 0;  // elements to drop
+  uint64_t lo = (uint64_t)v.x | ((uint64_t)v.y << 32), hi = (uint64_t)v.z | ((uint64_t)v.w << 32);
+  if (past >= 4) {
+    lo = hi;
+    hi = 0;
+  }
+  const int d = 16 * (past & 3);
+  lo = (lo >> d) | ((hi << 1) << (63 - d));
+  hi >>= d;
+  if (!ok || past == 8) lo = hi = 0;
+  return uint4{(uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32)};
 }
 
 __device__ __forceinline__ double block_sum(double v, double *lds) {
@@ -411,6 +447,156 @@ __global__ void __launch_bounds__(BS) to_nhwc_kernel(int c, int hw, const uint16
   *(uint4 *)(y + ((size_t)img * hw + p0 + p) * c + c0 + part * 8) = uint4{pk[0], pk[1], pk[2], pk[3]};
 }
 
+// The convolution for any shape with at most CP <= 384 input channels (padded to a
+// multiple of 16): a workgroup owns 64 output channels x 8 x 8 pixels, stages the
+// 10 x 10 halo with all its channels once (channel-last, zeros outside the image
+// and beyond cin), and its wavefronts walk k = (tap, channel) in steps of 16 as
+// conv_fwd_kernel does - the same matrix instructions in the same order, so for
+// cin % 16 == 0 the same bits - with the weights' fragments read ahead from
+// global memory.  That kernel's time is its staging: an index division and a
+// 2-byte load per element and tap.  4 x 48 x 50 x 75 -> 80 channels:
+// 62 us -> 16.7.
+constexpr int GT = 8, GH = GT + 2, AHEAD = 9;  // 9 divides the steps
+
+template <int CP, bool VEC>
+__global__ void __launch_bounds__(BS) conv_gen_kernel(int cin, int cout, int h, int w, const uint16_t *__restrict__ x,
+                                                     const uint16_t *__restrict__ wt, const float *__restrict__ bias,
+                                                     float *__restrict__ z, uint16_t *__restrict__ a,
+                                                     const uint16_t *__restrict__ mask) {
+  constexpr int S = CP + 4;  // LDS stride between pixels
+  __shared__ __attribute__((aligned(16))) uint16_t Xs[GH * GH * S];
+  const int n = blockIdx.z, nimg = gridDim.z, HW = h * w, K = cin * 9;
+  const int tilesx = (w + GT - 1) / GT;
+  const int y0 = (blockIdx.x / tilesx) * GT, x0 = (blockIdx.x % tilesx) * GT, co0 = blockIdx.y * TM;
+  const int t = threadIdx.x, wave = t >> 6, lane = t & 63, l16 = lane & 15, kq = lane >> 4;
+  const size_t cs = (size_t)nimg * HW;
+  const uint16_t *xn = x + (size_t)n * HW;
+  const int steps = (cin + 15) >> 4;  // a tap
+  // the lane's row of weights: channels 16 st + 4 kq .. + 3 of a tap, read where
+  // they are (or, past the last channel, from inside the row) AHEAD steps before
+  // they are used, zeroed past the last channel when they are used
+  const uint16_t *wr = wt + (size_t)min(co0 + 16 * wave + l16, cout - 1) * K;
+  auto load_a = [&](int tap, int st) {
+    const int c = 16 * st + 4 * kq;
+    if constexpr (VEC) {
+      return *(const uint2 *)(wr + min(tap, 8) * cin + min(c, cin - 4));
+    } else {
+      uint32_t e[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) e[j] = wr[min(tap, 8) * cin + min(c + j, cin - 1)];
+      return uint2{e[0] | (e[1] << 16), e[2] | (e[3] << 16)};
+    }
+  };
+  auto use_a = [&](uint2 v, int st) {
+    const int left = cin - (16 * st + 4 * kq);  // channels from here on
+    v.x = left >= 2 ? v.x : left == 1 ? v.x & 0xffffu : 0u;
+    v.y = left >= 4 ? v.y : left == 3 ? v.y & 0xffffu : 0u;
+    return __builtin_bit_cast(s4, v);
+  };
+  uint2 ar[AHEAD];
+  int ft = 0, fs = 0;  // the fragment to fetch next
+#pragma unroll
+  for (int u = 0; u < AHEAD; ++u) {
+    ar[u] = load_a(ft, fs);
+    if (++fs == steps) {
+      fs = 0;
+      ++ft;
+    }
+  }
+  // the lane's outputs (channels co4 .. + 3 of four pixels), their biases and mask
+  // values, read first: a load between the stores below would wait for them
+  const int co4 = co0 + 16 * wave + 4 * kq;
+  size_t pix[4];
+  bool okp[4];
+  float bv4[4];
+  uint16_t mk[4][4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) bv4[j] = bias ? bias[min(co4 + j, cout - 1)] : 0.f;
+#pragma unroll
+  for (int s = 0; s < 4; ++s) {
+    const int p = 16 * s + l16, y = y0 + (p >> 3), xx = x0 + (p & 7);
+    okp[s] = y < h && xx < w;
+    pix[s] = okp[s] ? (size_t)n * HW + (size_t)y * w + xx : 0;
+    if (a && mask) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) mk[s][j] = mask[(size_t)min(co4 + j, cout - 1) * cs + pix[s]];
+    }
+  }
+  // a halo row of two channels per thread and turn
+  for (int e = t; e < GH * 8 * steps; e += BS) {
+    const int c = 2 * (e / GH), r = e % GH, iy = y0 - 1 + r;
+    const bool ok = iy >= 0 && iy < h;
+    const uint16_t *r0 = xn + (size_t)min(c, cin - 1) * cs + (size_t)(ok ? iy : 0) * w;
+    const uint16_t *r1 = xn + (size_t)min(c + 1, cin - 1) * cs + (size_t)(ok ? iy : 0) * w;
+    uint4 v0 = raw8(r0, x0, w), v1 = raw8(r1, x0, w);
+    const int xl = max(x0 - 1, 0), xr = min(x0 + GT, w - 1);
+    const uint32_t l0 = r0[xl], l1 = r1[xl], e0 = r0[xr], e1 = r1[xr];
+    v0 = cut8(v0, x0, w, true);
+    v1 = cut8(v1, x0, w, true);
+    const uint32_t m0 = ok && c < cin ? 0xffffu : 0u, m1 = ok && c + 1 < cin ? 0xffff0000u : 0u;
+    uint16_t *d = Xs + r * GH * S + c;
+    *(uint32_t *)d = x0 > 0 ? (l0 & m0) | ((l1 << 16) & m1) : 0u;
+    const uint32_t u0[4] = {v0.x, v0.y, v0.z, v0.w}, u1[4] = {v1.x, v1.y, v1.z, v1.w};
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      *(uint32_t *)(d + (2 * q + 1) * S) = (u0[q] & m0) | ((u1[q] << 16) & m1);
+      *(uint32_t *)(d + (2 * q + 2) * S) = ((u0[q] >> 16) & m0) | (u1[q] & m1);
+    }
+    *(uint32_t *)(d + (GT + 1) * S) = x0 + GT < w ? (e0 & m0) | ((e1 << 16) & m1) : 0u;
+  }
+  __syncthreads();
+  f4 acc[4];
+#pragma unroll
+  for (int s = 0; s < 4; ++s) acc[s] = f4{0.f, 0.f, 0.f, 0.f};
+  const uint16_t *xb[4];  // pixel 16 s + l16 of the tile
+#pragma unroll
+  for (int s = 0; s < 4; ++s) xb[s] = Xs + ((2 * s + (l16 >> 3)) * GH + (l16 & 7)) * S + 4 * kq;
+  // the next step's pixels are read while this step multiplies
+  uint2 bn[4];
+  int st = 0, off = 0, kx = 0;
+#pragma unroll
+  for (int s = 0; s < 4; ++s) bn[s] = *(const uint2 *)xb[s];
+  for (int it = 0; it < steps; ++it) {
+#pragma unroll
+    for (int u = 0; u < AHEAD; ++u) {
+      const s4 av = use_a(ar[u], st);
+      uint2 b[4];
+#pragma unroll
+      for (int s = 0; s < 4; ++s) b[s] = bn[s];
+      off += 16;
+      if (++st == steps) {
+        st = 0;
+        off += S - 16 * steps;
+        if (++kx == 3) {
+          kx = 0;
+          off += (GH - 3) * S;
+        }
+      }
+      const int o = u == AHEAD - 1 && it == steps - 1 ? 0 : off;
+#pragma unroll
+      for (int s = 0; s < 4; ++s) bn[s] = *(const uint2 *)(xb[s] + o);
+      ar[u] = load_a(ft, fs);
+      if (++fs == steps) {
+        fs = 0;
+        ++ft;
+      }
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+        acc[s] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(av, __builtin_bit_cast(s4, b[s]), acc[s], 0, 0, 0);
+    }
+  }
+#pragma unroll
+  for (int s = 0; s < 4; ++s)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const float v = acc[s][j] + bv4[j];
+      if (!(okp[s] && co4 + j < cout)) continue;
+      const size_t o = (size_t)(co4 + j) * cs + pix[s];
+      if (z) z[o] = v;
+      if (a) a[o] = mask ? f2bf(bf2f(mk[s][j]) > 0.f ? v : 0.f) : f2bf(fmaxf(v, 0.f));
+    }
+}
+
 // The convolution of a one-channel input (cout <= 64): a workgroup of 64 x 4
 // pixels stages its 66 x 6 input halo and the weights in LDS; each thread
 // forms its pixel's cout outputs as FP32 sums over the taps in order (plus
@@ -473,7 +659,8 @@ uint16_t *nhwc_buffer(size_t elems, hipStream_t s) {
 
 // One forward convolution launch: the LDS-tiled kernel where the shape and
 // the weight alignment allow it (its input staged from a channel-last copy,
-// 16-byte loads of a pixel's channels), else the generic one.
+// 16-byte loads of a pixel's channels), else the one for any shape, or, beyond
+// 384 input channels, the one that stages a step at a time.
 void launch_conv(int n, int cin, int cout, int h, int w, const uint16_t *x, const uint16_t *wt, const float *bias,
                  float *z, uint16_t *a, const uint16_t *mask, hipStream_t s) {
   if (cin == 1 && cout <= 64) {
@@ -502,65 +689,19 @@ void launch_conv(int n, int cin, int cout, int h, int w, const uint16_t *x, cons
       hipLaunchKernelGGL((conv_fwd_mfma_kernel<4>), g, dim3(BS), 0, s, cin, cout, h, w, xh, wt, bias, z, a, mask);
     return;
   }
+  if (cin <= 384) {  // the halo of all channels fits the LDS
+    const dim3 g(((h + GT - 1) / GT) * ((w + GT - 1) / GT), (cout + TM - 1) / TM, n);
+    auto pick = [&](auto vec) {
+      constexpr bool V = decltype(vec)::value;
+      return cin <= 64 ? &conv_gen_kernel<64, V> : cin <= 128 ? &conv_gen_kernel<128, V>
+             : cin <= 256 ? &conv_gen_kernel<256, V> : &conv_gen_kernel<384, V>;
+    };
+    auto *k = cin % 4 == 0 && ((uintptr_t)wt & 7) == 0 ? pick(std::true_type()) : pick(std::false_type());
+    hipLaunchKernelGGL(k, g, dim3(BS), 0, s, cin, cout, h, w, x, wt, bias, z, a, mask);
+    return;
+  }
   const dim3 g((h * w + TN - 1) / TN, (cout + TM - 1) / TM, n);
   hipLaunchKernelGGL(conv_fwd_kernel, g, dim3(BS), 0, s, cin, cout, h, w, x, wt, bias, z, a, mask);
-}
-
-// Partial weight gradients over one range of pixels q = (n, p) of the batch:
-// part[split][co][k] = sum_q dz[co][q] xhat[k][q].  grid (ceil(K/64), ceil(cout/64), splits).
-__global__ void __launch_bounds__(BS) conv_wgrad_kernel(int nimg, int cin, int cout, int h, int w,
-                                                       const uint16_t *__restrict__ x, const uint16_t *__restrict__ dz,
-                                                       float *__restrict__ part, int chunk) {
-  __shared__ uint16_t As[TM][TK + PAD];  // dz: co x q
-  __shared__ uint16_t Bs[TK][TN + PAD];  // xhat: q x k
-  const int HW = h * w, K = cin * 9;
-  const int64_t P = (int64_t)nimg * HW;
-  const int k0 = blockIdx.x * TN, co0 = blockIdx.y * TM, split = blockIdx.z;
-  const int64_t qb = (int64_t)split * chunk, qe = min(P, qb + chunk);
-  const int t = threadIdx.x, wave = t >> 6, lane = t & 63;
-  f4 acc[4];
-#pragma unroll
-  for (int s = 0; s < 4; ++s) acc[s] = f4{0.f, 0.f, 0.f, 0.f};
-  for (int64_t q0 = qb; q0 < qe; q0 += TK) {
-    {
-      const int r = t >> 2, c = (t & 3) * 4, co = co0 + r;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int64_t q = q0 + c + j;
-        As[r][c + j] = (co < cout && q < qe) ? dz[(size_t)co * P + q] : (uint16_t)0;
-      }
-    }
-    {
-      const int qq = t >> 4, c = (t & 15) * 4;
-      const int64_t q = q0 + qq;
-      const bool qok = q < qe;
-      const int64_t n = qok ? q / HW : 0;
-      const int p = qok ? (int)(q - n * HW) : 0;
-      const int y = p / w, xx = p - y * w;
-      const uint16_t *xn = x + (size_t)n * HW;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int k = k0 + c + j;
-        uint16_t v = 0;
-        if (qok && k < K) {
-          const int tap = k / cin, ci = k - tap * cin, ky = tap / 3, kx = tap - ky * 3;
-          const int iy = y + ky - 1, ix = xx + kx - 1;
-          if (iy >= 0 && iy < h && ix >= 0 && ix < w) v = xn[(size_t)ci * P + iy * w + ix];
-        }
-        Bs[qq][c + j] = v;
-      }
-    }
-    __syncthreads();
-    mfma_step(As, Bs, wave, lane, acc);
-    __syncthreads();
-  }
-#pragma unroll
-  for (int s = 0; s < 4; ++s)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int co = co0 + 16 * wave + 4 * (lane >> 4) + j, k = k0 + 16 * s + (lane & 15);
-      if (co < cout && k < K) part[((size_t)split * cout + co) * K + k] = acc[s][j];
-    }
 }
 
 // Weight gradient, LDS-tiled for cin % 32 == 0, h % 8 == 0, w % 16 == 0 and
@@ -578,11 +719,15 @@ __global__ void __launch_bounds__(BS) conv_wgrad_kernel(int nimg, int cin, int c
 // With bpart, the workgroups of the first input chunk also write the
 // split's bias partial sums bpart[split * stride + co] = sum of dz[co][q]
 // over its tiles.  grid (ceil(cout/CT), cin/32, splits).
+// RAG: any shape and alignment: tiles and channels may hang over (zeros there),
+// rows are loaded by raw8, and the bias sums are kept in FP64.  The
+// kernel it replaces formed an index by division per element and matrix step:
+// 4 x (48 -> 80) x 50 x 75 46 us -> 19.
 constexpr int GY = 8, GX = 16, GP = GY * GX;  // pixel tile
 constexpr int DST = GP + 8;                   // LDS stride of staged dz rows
 constexpr int XCI = (GY + 2) * GX + 8;        // LDS stride per input channel of a shifted copy
 
-template <int CT>
+template <int CT, bool RAG>
 __global__ void __launch_bounds__(BS) conv_wgrad_mfma_kernel(int nimg, int cin, int cout, int h, int w,
                                                             const uint16_t *__restrict__ x,
                                                             const uint16_t *__restrict__ dz,
@@ -595,7 +740,7 @@ __global__ void __launch_bounds__(BS) conv_wgrad_mfma_kernel(int nimg, int cin, 
   const int HW = h * w;
   const size_t P = (size_t)nimg * HW;
   const int co0 = blockIdx.x * CT, ci0 = blockIdx.y * 32, split = blockIdx.z;
-  const int tx_n = w / GX, tiles_img = (h / GY) * tx_n, tiles = nimg * tiles_img;
+  const int tx_n = (w + GX - 1) / GX, tiles_img = ((h + GY - 1) / GY) * tx_n, tiles = nimg * tiles_img;
   const int T0 = split * tiles_per_split, T1 = min(tiles, T0 + tiles_per_split);
   const int t = threadIdx.x, wave = t >> 6, lane = t & 63, l16 = lane & 15, kq = lane >> 4;
   const int cw = CT == 64 ? wave : (wave & 1), nb = CT == 64 ? 0 : (wave >> 1);
@@ -605,9 +750,10 @@ __global__ void __launch_bounds__(BS) conv_wgrad_mfma_kernel(int nimg, int cin, 
   for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
     for (int tp = 0; tp < 9; ++tp) acc[nt][tp] = f4{0.f, 0.f, 0.f, 0.f};
-  float bacc[DV];
+  using B = std::conditional_t<RAG, double, float>;
+  B bacc[DV];
 #pragma unroll
-  for (int k = 0; k < DV; ++k) bacc[k] = 0.f;
+  for (int k = 0; k < DV; ++k) bacc[k] = 0;
   // A tile's global loads, issued together into registers: the dz rows (CT
   // channels x 8 rows x 16 pixels as 16-byte vectors) and the input halo
   // rows y0-1 .. y0+8 of the 32 channels (one row per thread and pass: the
@@ -616,15 +762,23 @@ __global__ void __launch_bounds__(BS) conv_wgrad_mfma_kernel(int nimg, int cin, 
   constexpr int XR = (32 * (GY + 2) + BS - 1) / BS;
   uint4 dv[DV], xa[XR], xb[XR];
   uint32_t xl[XR], xr[XR];
+  bool okd[DV], okx[XR];  // RAG: the row exists; the loaded rows are cut when they are stored
+  int cx0 = 0;
   auto load_tile = [&](int T) {
     const int n = T / tiles_img, rem = T - n * tiles_img;
     const int y0 = (rem / tx_n) * GY, x0 = (rem % tx_n) * GX;
+    cx0 = x0;
 #pragma unroll
     for (int k = 0; k < DV; ++k) {
       const int v = t + k * BS;
       const int half = v & 1, r = (v >> 1) & (GY - 1), co = co0 + (v >> 4);
       dv[k] = uint4{0u, 0u, 0u, 0u};
-      if (co < cout) dv[k] = *(const uint4 *)(dz + (size_t)co * P + (size_t)n * HW + (size_t)(y0 + r) * w + x0 + 8 * half);
+      if constexpr (RAG) {
+        const bool ok = co < cout && y0 + r < h;
+        const uint16_t *row = dz + (ok ? (size_t)co * P + (size_t)n * HW + (size_t)(y0 + r) * w : 0);
+        dv[k] = raw8(row, x0 + 8 * half, w);
+        okd[k] = ok;
+      } else if (co < cout) dv[k] = *(const uint4 *)(dz + (size_t)co * P + (size_t)n * HW + (size_t)(y0 + r) * w + x0 + 8 * half);
     }
 #pragma unroll
     for (int q = 0; q < XR; ++q) {
@@ -632,7 +786,15 @@ __global__ void __launch_bounds__(BS) conv_wgrad_mfma_kernel(int nimg, int cin, 
       xa[q] = xb[q] = uint4{0u, 0u, 0u, 0u};
       xl[q] = xr[q] = 0u;
       const int c = rr / (GY + 2), r = rr - c * (GY + 2), iy = y0 - 1 + r;
-      if (rr < 32 * (GY + 2) && iy >= 0 && iy < h) {
+      if constexpr (RAG) {
+        const bool ok = rr < 32 * (GY + 2) && ci0 + c < cin && iy >= 0 && iy < h;
+        const uint16_t *row = x + (ok ? (size_t)(ci0 + c) * P + (size_t)n * HW + (size_t)iy * w : 0);
+        xa[q] = raw8(row, x0, w);
+        xb[q] = raw8(row, x0 + 8, w);
+        xl[q] = row[max(x0 - 1, 0)];
+        xr[q] = row[min(x0 + GX, w - 1)];
+        okx[q] = ok;
+      } else if (rr < 32 * (GY + 2) && iy >= 0 && iy < h) {
         const uint16_t *row = x + (size_t)(ci0 + c) * P + (size_t)n * HW + (size_t)iy * w;
         xa[q] = *(const uint4 *)(row + x0);
         xb[q] = *(const uint4 *)(row + x0 + 8);
@@ -644,6 +806,17 @@ __global__ void __launch_bounds__(BS) conv_wgrad_mfma_kernel(int nimg, int cin, 
   // ... and their LDS copies: dz rows as they are, the input rows three
   // times, shifted by kx (copy kx, pixel q = input column x0 - 1 + q + kx)
   auto store_tile = [&]() {
+    if constexpr (RAG) {
+#pragma unroll
+      for (int k = 0; k < DV; ++k) dv[k] = cut8(dv[k], cx0 + 8 * (t & 1), w, okd[k]);
+#pragma unroll
+      for (int q = 0; q < XR; ++q) {
+        xa[q] = cut8(xa[q], cx0, w, okx[q]);
+        xb[q] = cut8(xb[q], cx0 + 8, w, okx[q]);
+        xl[q] = okx[q] && cx0 > 0 ? xl[q] : 0u;
+        xr[q] = okx[q] && cx0 + GX < w ? xr[q] : 0u;
+      }
+    }
 #pragma unroll
     for (int k = 0; k < DV; ++k) {
       const int v = t + k * BS;
@@ -651,9 +824,9 @@ __global__ void __launch_bounds__(BS) conv_wgrad_mfma_kernel(int nimg, int cin, 
       *(uint4 *)(Ds + c * DST + r * GX + 8 * half) = dv[k];
       if (with_bias) {
         const uint32_t u[4] = {dv[k].x, dv[k].y, dv[k].z, dv[k].w};
-        float s8 = 0.f;
+        B s8 = 0;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) s8 += bf2f((uint16_t)(u[j] & 0xffffu)) + bf2f((uint16_t)(u[j] >> 16));
+        for (int j = 0; j < 4; ++j) s8 += (B)bf2f((uint16_t)(u[j] & 0xffffu)) + (B)bf2f((uint16_t)(u[j] >> 16));
         bacc[k] += s8;
       }
     }
@@ -709,18 +882,18 @@ __global__ void __launch_bounds__(BS) conv_wgrad_mfma_kernel(int nimg, int cin, 
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         const int co = co0 + 16 * cw + 4 * kq + j, ci = ci0 + 16 * (nb + nt) + l16;
-        if (co < cout) part[(size_t)split * stride + ((size_t)co * 9 + tp) * cin + ci] = acc[nt][tp][j];
+        if (co < cout && (!RAG || ci < cin)) part[(size_t)split * stride + ((size_t)co * 9 + tp) * cin + ci] = acc[nt][tp][j];
       }
   if (with_bias) {
     // the 16 consecutive lanes that staged one channel's rows, summed in a
     // fixed butterfly order
 #pragma unroll
     for (int k = 0; k < DV; ++k) {
-      float v = bacc[k];
+      B v = bacc[k];
 #pragma unroll
       for (int o = 8; o > 0; o >>= 1) v += __shfl_xor(v, o, 16);
       const int co = co0 + (t >> 4) + 16 * k;
-      if ((t & 15) == 0 && co < cout) bpart[(size_t)split * stride + co] = v;
+      if ((t & 15) == 0 && co < cout) bpart[(size_t)split * stride + co] = (float)v;
     }
   }
 }
@@ -797,15 +970,27 @@ __global__ void __launch_bounds__(BS) conv1_wgrad_kernel(int nimg, int cout, int
   }
 }
 
-// Split plan of the weight gradient: which kernel, how many partial sums,
-// pixels (generic) or pixel tiles (tiled) per split.
+// Split plan of the weight gradient: which kernel, how many partial sums, pixel
+// tiles per split.
 struct WgradPlan {
-  bool tiled, c1;  // LDS-tiled matrix-core kernel; one-input-channel kernel
+  bool tiled, c1;  // 16-byte loads of whole tiles; one-input-channel kernel
   int splits, chunk;
 };
 
 // Output-channel tile of the tiled weight gradient.
 inline int wgrad_ct(int cout) { return cout <= 32 ? 32 : 64; }
+
+// The splits that the workspace of a ragged shape has room for: 768 workgroups of
+// 64 x 64 weights, at least 256 pixels each.
+int wgrad_splits(int n, int cin, int cout, int h, int w) {
+  const int64_t P = (int64_t)n * h * w;
+  const int64_t groups = (int64_t)((cin * 9 + TN - 1) / TN) * ((cout + TM - 1) / TM);
+  const int64_t want = std::max<int64_t>(1, (768 + groups - 1) / groups);
+  const int splits = (int)std::min<int64_t>(want, std::max<int64_t>(1, (P + 255) / 256));
+  int64_t chunk = (P + splits - 1) / splits;
+  chunk = (chunk + TK - 1) / TK * TK;
+  return (int)((P + chunk - 1) / chunk);
+}
 
 // About 768 workgroups in flight (three per CU), at least two pixel tiles
 // per tiled workgroup so the partial sums stay few.
@@ -829,19 +1014,17 @@ WgradPlan wgrad_plan(int n, int cin, int cout, int h, int w) {
     pl.splits = (tiles + per - 1) / per;
     return pl;
   }
-  const int64_t P = (int64_t)n * h * w;
-  const int64_t groups = (int64_t)((cin * 9 + TN - 1) / TN) * ((cout + TM - 1) / TM);
-  const int64_t want = std::max<int64_t>(1, (768 + groups - 1) / groups);
-  pl.tiled = false;
-  pl.splits = (int)std::min<int64_t>(want, std::max<int64_t>(1, (P + 255) / 256));
-  int64_t chunk = (P + pl.splits - 1) / pl.splits;
-  chunk = (chunk + TK - 1) / TK * TK;
-  pl.chunk = (int)chunk;
-  pl.splits = (int)((P + chunk - 1) / chunk);
+  // ragged shapes: as many workgroups, at most the splits of wgrad_splits
+  const int ct = wgrad_ct(cout);
+  const int64_t groups = (int64_t)((cout + ct - 1) / ct) * ((cin + 31) / 32);
+  const int64_t tiles = (int64_t)n * ((h + GY - 1) / GY) * ((w + GX - 1) / GX);
+  const int64_t want = std::max<int64_t>(1, std::min<int64_t>((768 + groups - 1) / groups, wgrad_splits(n, cin, cout, h, w)));
+  pl.chunk = (int)((tiles + want - 1) / want);
+  pl.splits = (int)((tiles + pl.chunk - 1) / pl.chunk);
   return pl;
 }
 
-// Pixel ranges of the bias-gradient reduction of the generic kernel.
+// Bias sums that the workspace of a ragged shape has room for, beside its splits.
 int64_t bias_ranges(int64_t P) { return std::min<int64_t>(64, std::max<int64_t>(1, (P + 16383) / 16384)); }
 
 // out[i] = sum over k < splits of part[k * stride + i], i < m.  G groups of
@@ -884,21 +1067,6 @@ void launch_split_sum(const float *part, int splits, int64_t stride, int64_t m, 
     hipLaunchKernelGGL(split_sum_kernel<4>, g, dim3(64 * 4), 0, s, part, splits, stride, m, out);
   else
     hipLaunchKernelGGL(split_sum_kernel<1>, g, dim3(64), 0, s, part, splits, stride, m, out);
-}
-
-// Partial bias gradients: part[b][co] = sum of dz[co][q] over pixel range b
-// (FP64 within the range).  grid (cout, ranges).
-__global__ void __launch_bounds__(BS) bias_grad_kernel(int64_t P, int64_t chunk, const uint16_t *__restrict__ dz,
-                                                      float *__restrict__ part) {
-  __shared__ double lds[BS / 64];
-  const int co = blockIdx.x, b = blockIdx.y;
-  const int64_t q0 = (int64_t)b * chunk, q1 = min(P, q0 + chunk);
-  const uint16_t *row = dz + (size_t)co * P;
-  double v = 0;
-#pragma unroll 8
-  for (int64_t q = q0 + threadIdx.x; q < q1; q += BS) v += bf2f(row[q]);
-  const double s = block_sum(v, lds);
-  if (threadIdx.x == 0) part[(size_t)b * gridDim.x + co] = (float)s;
 }
 
 // wrot[ci][ky][kx][co] = w[co][2-ky][2-kx][ci]: the data gradient is the
@@ -1272,9 +1440,10 @@ fdtd_status fdtd_nn_rot_weights(int32_t nlayers, const int32_t *cin, const int32
 
 int64_t fdtd_nn_wgrad_work(int32_t n, int32_t cin, int32_t cout, int32_t h, int32_t w) {
   if (n <= 0 || cin <= 0 || cout <= 0 || h <= 0 || w <= 0) return 0;
-  const int64_t P = (int64_t)n * h * w, splits = wgrad_plan(n, cin, cout, h, w).splits;
-  // tiled: splits rows of cout * cin * 9 weight and cout bias sums; generic:
-  // the weight rows, then bias_ranges(P) rows of cout bias sums
+  const WgradPlan pl = wgrad_plan(n, cin, cout, h, w);
+  const int64_t P = (int64_t)n * h * w, splits = pl.c1 || pl.tiled ? pl.splits : wgrad_splits(n, cin, cout, h, w);
+  // splits rows of cout * cin * 9 weight and cout bias sums (a ragged shape's may
+  // be fewer)
   return splits * cout * cin * 9 + std::max(splits, bias_ranges(P)) * cout;
 }
 
@@ -1294,53 +1463,27 @@ namespace {
 // fdtd_nn_wgrad_work floats; every slot the reductions read is written first).
 void wgrad_run(int32_t n, int32_t cin, int32_t cout, int32_t h, int32_t w, const uint16_t *x, const uint16_t *dz,
                float *dw, float *db, float *work, hipStream_t s) {
-    const int K = cin * 9;
-    const int64_t P = (int64_t)n * h * w;
+    const int64_t m = (int64_t)cout * cin * 9, stride = m + cout;
     const WgradPlan pl = wgrad_plan(n, cin, cout, h, w);
-    const int64_t m = (int64_t)cout * K;
+    // partial rows [split][m weight sums | cout bias sums]
+    float *bp = db ? work + m : nullptr;
     if (pl.c1) {
-      // partial rows [split][m weight sums | cout bias sums]
-      const int64_t stride = m + cout;
       hipLaunchKernelGGL(conv1_wgrad_kernel, dim3(pl.splits), dim3(BS), 0, s, n, cout, h, w, x, dz, work, stride,
-                         pl.chunk, db ? work + m : nullptr);
-      if (db && db == dw + m) {
-        launch_split_sum(work, pl.splits, stride, m + cout, dw, s);
-      } else {
-        launch_split_sum(work, pl.splits, stride, m, dw, s);
-        if (db) launch_split_sum(work + m, pl.splits, stride, cout, db, s);
-      }
-    } else if (pl.tiled && ((uintptr_t)dz & 15) == 0 && ((uintptr_t)x & 15) == 0) {
-      // partial rows [split][m weight sums | cout bias sums]
-      const int64_t stride = m + cout;
-      const int ct = wgrad_ct(cout);
-      const dim3 g((cout + ct - 1) / ct, cin / 32, pl.splits);
-      float *bp = db ? work + m : nullptr;
-      if (ct == 32)
-        hipLaunchKernelGGL(conv_wgrad_mfma_kernel<32>, g, dim3(BS), 0, s, n, cin, cout, h, w, x, dz, work, stride,
-                           pl.chunk, bp);
-      else
-        hipLaunchKernelGGL(conv_wgrad_mfma_kernel<64>, g, dim3(BS), 0, s, n, cin, cout, h, w, x, dz, work, stride,
-                           pl.chunk, bp);
-      if (db && db == dw + m) {  // contiguous weight and bias gradients: one reduction
-        launch_split_sum(work, pl.splits, stride, m + cout, dw, s);
-      } else {
-        launch_split_sum(work, pl.splits, stride, m, dw, s);
-        if (db) launch_split_sum(work + m, pl.splits, stride, cout, db, s);
-      }
+                         pl.chunk, bp);
     } else {
-      // generic kernel, at most as many pixel ranges as the plan has partial sums
-      int64_t chunk = (P + pl.splits - 1) / pl.splits;
-      chunk = (chunk + TK - 1) / TK * TK;
-      const int S = (int)((P + chunk - 1) / chunk);
-      const dim3 g((K + TN - 1) / TN, (cout + TM - 1) / TM, S);
-      hipLaunchKernelGGL(conv_wgrad_kernel, g, dim3(BS), 0, s, n, cin, cout, h, w, x, dz, work, (int)chunk);
-      launch_split_sum(work, S, m, m, dw, s);
-      if (db) {
-        float *pb = work + (size_t)pl.splits * m;
-        const int64_t nr = bias_ranges(P), bchunk = (P + nr - 1) / nr;
-        hipLaunchKernelGGL(bias_grad_kernel, dim3(cout, (unsigned)nr), dim3(BS), 0, s, P, bchunk, dz, pb);
-        launch_split_sum(pb, (int)nr, cout, cout, db, s);
-      }
+      // (whole tiles at odd addresses are loaded element by element, like ragged ones)
+      const bool vec = pl.tiled && ((uintptr_t)dz & 15) == 0 && ((uintptr_t)x & 15) == 0;
+      const int ct = wgrad_ct(cout);
+      const dim3 g((cout + ct - 1) / ct, (cin + 31) / 32, pl.splits);
+      auto *k = ct == 32 ? (vec ? &conv_wgrad_mfma_kernel<32, false> : &conv_wgrad_mfma_kernel<32, true>)
+                         : (vec ? &conv_wgrad_mfma_kernel<64, false> : &conv_wgrad_mfma_kernel<64, true>);
+      hipLaunchKernelGGL(k, g, dim3(BS), 0, s, n, cin, cout, h, w, x, dz, work, stride, pl.chunk, bp);
+    }
+    if (db && db == dw + m) {  // contiguous weight and bias gradients: one reduction
+      launch_split_sum(work, pl.splits, stride, m + cout, dw, s);
+    } else {
+      launch_split_sum(work, pl.splits, stride, m, dw, s);
+      if (db) launch_split_sum(work + m, pl.splits, stride, cout, db, s);
     }
     FDTD_HIP(hipGetLastError());
 }
