@@ -29,6 +29,13 @@ typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
 constexpr int BS = 256;
 constexpr int TM = 64, TN = 64, TK = 16, PAD = 4;
 
+// Workgroups go round-robin over the 8 XCDs, each with its own L2; neighbouring
+// work items (tiles that share 128-byte lines of a row, output-channel blocks of
+// one tile) belong on one XCD.  Item of workgroup b of a grid of xcd_grid(items):
+// XCD b % 8 takes items (b % 8) * grid / 8 onwards, in order.
+__device__ __forceinline__ int xcd_item(int b, int grid) { return (b & 7) * (grid >> 3) + (b >> 3); }
+unsigned xcd_grid(int64_t items) { return (unsigned)((items + 7) / 8 * 8); }
+
 // IEEE binary32 -> bfloat16, round to nearest even (NaN kept quiet).
 __device__ __forceinline__ uint16_t f2bf(float f) {
   uint32_t u = __float_as_uint(f);
@@ -217,144 +224,94 @@ __global__ void __launch_bounds__(BS) conv_fwd_kernel(int cin, int cout, int h, 
     }
 }
 
-// The same convolution, LDS-tiled for cin % 32 == 0 and h, w multiples of 16,
-// on v_mfma_f32_16x16x32_bf16, reading a channel-last copy of the input
-// (x[n][y][x][cin], to_nhwc_kernel).  A workgroup owns 16*MT output channels
-// x a 16 x 16 pixel tile of one image; per chunk of 32 input channels it
-// stages the 18 x 18 halo tile in LDS (a pixel's 32 channels are four
-// 16-byte loads; eight channels of one pixel are one 16-byte LDS read) and
-// the weights of all nine taps, then each
-// wavefront (four pixel rows) runs nine taps x MT x 4 matrix instructions.
-// grid ((h/16) * (w/16), ceil(cout / (16*MT)), n).
-// Pipelined variant: a workgroup walks `tpw` pixel tiles; the next (tile,
-// chunk)'s input (and, with several chunks, its weights) is loaded into
-// registers before the current chunk's matrix instructions and written to
-// LDS after them; grid (ceil(tiles / tpw), ceil(cout / (16*MT)), n).
+// The same convolution, LDS-tiled for cin % 32 == 0, h, w multiples of 16 and
+// 16-byte aligned x and weights, on v_mfma_f32_16x16x32_bf16.  A workgroup owns
+// 32 output channels x 16 x 16 pixels of one image; per chunk of 32 input
+// channels it stages the 18 x 18 halo tile channel-last in LDS (eight channels of
+// one pixel are one 16-byte LDS read) and the weights of all nine taps, then each
+// wavefront (four pixel rows) runs nine taps x 2 x 4 matrix instructions.  What
+// bounds it is the wait for the staged data: all of a chunk's loads are issued
+// together, the next chunk's before the current one's matrix instructions.  A
+// thread loads a halo row of two channels (the channel pairs of a row on
+// neighbouring lanes: their LDS writes fall into one pixel's row); the last two
+// rows, which 256 threads leave over, go by 16-byte pieces.  One chunk (ONE) holds
+// 96 registers instead of 198: three workgroups a CU.  32 images of 128^2:
+// 32 -> 32 channels 40 us and 9 to 14 for a channel-last copy -> 28;
+// 16^2, 256 -> 256 35 us and 5 -> 22 (blocks of 64 channels left half of the CUs
+// idle there, and at 64^2, 64 -> 192 took 92 us against 70).
+// One-dimensional grid of xcd_grid((h/16) * (w/16) * ceil(cout / 32) * n).
 constexpr int CC = 32;                  // input channels per chunk
+constexpr int MT = 2;                   // output channels of a workgroup / 16
 constexpr int XST = 40;                 // LDS stride between staged pixels (80 B: conflict-free 16 B reads)
 constexpr int WST = 40;                 // LDS stride between staged (tap, co) weight rows
 constexpr int TT = 16, HT = TT + 2;     // output tile side, halo tile side
 
-template <int MT>
+template <bool ONE>
 __global__ void __launch_bounds__(BS) conv_fwd_mfma_kernel(int cin, int cout, int h, int w,
-                                                          const uint16_t *__restrict__ x,
-                                                          const uint16_t *__restrict__ wt,
-                                                          const float *__restrict__ bias, float *__restrict__ z,
-                                                          uint16_t *__restrict__ a,
-                                                          const uint16_t *__restrict__ mask) {
-  __shared__ __attribute__((aligned(16))) uint16_t Xs[HT * HT * XST];
-  __shared__ __attribute__((aligned(16))) uint16_t Ws[9 * 16 * MT * WST];
-  const int n = blockIdx.z, nimg = gridDim.z, HW = h * w;
-  const int tilesx = w / TT;
-  const int y0 = (blockIdx.x / tilesx) * TT, x0 = (blockIdx.x % tilesx) * TT;
-  const int co0 = blockIdx.y * 16 * MT;
-  const int t = threadIdx.x, wave = t >> 6, lane = t & 63, l16 = lane & 15, kq = lane >> 4;
-  const size_t cs = (size_t)nimg * HW;
-  f4 acc[MT][4];
-#pragma unroll
-  for (int m = 0; m < MT; ++m)
-#pragma unroll
-    for (int s = 0; s < 4; ++s) acc[m][s] = f4{0.f, 0.f, 0.f, 0.f};
-  // a data-gradient pass's mask values, loaded first so that they arrive
-  // while the tile is staged and multiplied
-  const size_t pix0 = (size_t)n * HW + (size_t)(y0 + 4 * wave) * w + x0 + l16;
-  const bool masked = a && mask;
-  uint16_t mk[MT][4][4];
-  if (masked) {
-#pragma unroll
-    for (int m = 0; m < MT; ++m) load_mask16(mk[m], co0 + 16 * m, cout, kq, pix0, w, cs, mask);
-  }
-  for (int c0 = 0; c0 < cin; c0 += CC) {
-    for (int v = t; v < 9 * 16 * MT * 4; v += BS) {
-      const int part = v & 3, row = v >> 2;
-      const int tap = row / (16 * MT), col = row - tap * (16 * MT), co = co0 + col;
-      uint4 val = {0u, 0u, 0u, 0u};
-      if (co < cout) val = *(const uint4 *)(wt + ((size_t)co * 9 + tap) * cin + c0 + 8 * part);
-      *(uint4 *)(Ws + row * WST + 8 * part) = val;
-    }
-    // one halo pixel per thread: its 32 channels, packed into 16-byte LDS writes
-    for (int pos = t; pos < HT * HT; pos += BS) {
-      const int r = pos / HT, q = pos - r * HT;
-      const int iy = y0 - 1 + r, ix = x0 - 1 + q;
-      const bool ok = iy >= 0 && iy < h && ix >= 0 && ix < w;
-      // channel-last input: the pixel's 32 channels are 64 contiguous bytes
-      const uint4 *src = (const uint4 *)(x + ((size_t)n * HW + (ok ? iy * w + ix : 0)) * cin + c0);
-#pragma unroll
-      for (int c8 = 0; c8 < CC / 8; ++c8)
-        *(uint4 *)(Xs + pos * XST + 8 * c8) = ok ? src[c8] : uint4{0u, 0u, 0u, 0u};
-    }
-    __syncthreads();
-#pragma unroll
-    for (int tap = 0; tap < 9; ++tap) {
-      const int ky = tap / 3, kx = tap - 3 * ky;
-      bf8 av[MT], bv[4];
-#pragma unroll
-      for (int m = 0; m < MT; ++m) av[m] = *(const bf8 *)(Ws + (tap * 16 * MT + 16 * m + l16) * WST + 8 * kq);
-#pragma unroll
-      for (int s = 0; s < 4; ++s) bv[s] = *(const bf8 *)(Xs + ((4 * wave + s + ky) * HT + l16 + kx) * XST + 8 * kq);
-#pragma unroll
-      for (int m = 0; m < MT; ++m)
-#pragma unroll
-        for (int s = 0; s < 4; ++s) acc[m][s] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[m], bv[s], acc[m][s], 0, 0, 0);
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int m = 0; m < MT; ++m) tile_out16(acc[m], mk[m], masked, co0 + 16 * m, cout, kq, pix0, w, cs, bias, z, a);
-}
-
-// The same with the staging software-pipelined (see above): faster on the
-// deep layers with a few pixel tiles and several channel chunks, slower on
-// the wide ones (its prefetch registers leave one wavefront per SIMD).
-template <int MT>
-__global__ void __launch_bounds__(BS) conv_fwd_mfma_pipe_kernel(int cin, int cout, int h, int w,
                                                                const uint16_t *__restrict__ x,
                                                                const uint16_t *__restrict__ wt,
                                                                const float *__restrict__ bias,
                                                                float *__restrict__ z, uint16_t *__restrict__ a,
-                                                               const uint16_t *__restrict__ mask, const int tpw) {
+                                                               const uint16_t *__restrict__ mask, const int nimg) {
   __shared__ __attribute__((aligned(16))) uint16_t Xs[HT * HT * XST];
   __shared__ __attribute__((aligned(16))) uint16_t Ws[9 * 16 * MT * WST];
-  constexpr int NXP = (HT * HT + BS - 1) / BS;           // halo pixels per thread (2)
   constexpr int NWV = (9 * 16 * MT * 4 + BS - 1) / BS;   // 16-byte weight vectors per thread
-  const int n = blockIdx.z, nimg = gridDim.z, HW = h * w;
-  const int tilesx = w / TT, tiles = (h / TT) * tilesx;
-  const int tb = blockIdx.x * tpw, te = min(tiles, tb + tpw);
-  const int nch = cin / CC, steps = (te - tb) * nch;  // (pixel tile, channel chunk), chunk fastest
-  const int co0 = blockIdx.y * 16 * MT;
+  const int HW = h * w;
+  const int tilesx = w / TT, tiles = (h / TT) * tilesx, cot = (cout + 16 * MT - 1) / (16 * MT);
+  const int item = xcd_item(blockIdx.x, gridDim.x), n = item / (cot * tiles);
+  if (n >= nimg) return;
+  const int tile = item / cot % tiles, steps = ONE ? 1 : cin / CC;
+  const int co0 = item % cot * 16 * MT;
   const int t = threadIdx.x, wave = t >> 6, lane = t & 63, l16 = lane & 15, kq = lane >> 4;
   const size_t cs = (size_t)nimg * HW;
-  uint32_t xr[NXP][CC / 2];
-  uint4 wr[NWV];
-  // global -> registers for step (tile, c0); registers -> LDS after the barrier
-  auto load_x = [&](int tile, int c0) {
-    const int y0 = (tile / tilesx) * TT, x0 = (tile % tilesx) * TT;
-#pragma unroll
-    for (int k = 0; k < NXP; ++k) {
-      const int pos = t + k * BS;
-      const int r = pos / HT, q = pos - r * HT;
-      const int iy = y0 - 1 + r, ix = x0 - 1 + q;
-      const bool ok = pos < HT * HT && iy >= 0 && iy < h && ix >= 0 && ix < w;
-      const uint4 *src = (const uint4 *)(x + ((size_t)n * HW + (ok ? iy * w + ix : 0)) * cin + c0);
-#pragma unroll
-      for (int c8 = 0; c8 < CC / 8; ++c8) {
-        const uint4 v = ok ? src[c8] : uint4{0u, 0u, 0u, 0u};
-        xr[k][4 * c8] = v.x;
-        xr[k][4 * c8 + 1] = v.y;
-        xr[k][4 * c8 + 2] = v.z;
-        xr[k][4 * c8 + 3] = v.w;
-      }
+  uint4 xv[4], xt = {0u, 0u, 0u, 0u}, wr[NWV];
+  uint32_t xe[4], te2 = 0;  // halo columns
+  // rows 0 .. 15: channels c, c + 1 of row r; rows 16, 17: 8 pixels of channel tc
+  const int c = 2 * (t & 15), r = t >> 4, tc = (t >> 1) & 31, tr = 16 + (t >> 6), th = t & 1;
+  int lx0 = 0, ly0 = 0;  // the loaded tile's origin
+  // global -> registers for the chunk at channel c0; registers -> LDS after the barrier
+  auto load_x = [&](int c0) {
+    ly0 = (tile / tilesx) * TT;
+    lx0 = (tile % tilesx) * TT;
+    const int xl = max(lx0 - 1, 0), xr = min(lx0 + TT, w - 1);
+    const uint16_t *r0 = x + (size_t)(c0 + c) * cs + (size_t)n * HW + (size_t)max(ly0 - 1 + r, 0) * w;
+    const uint16_t *r1 = r0 + cs;
+    xv[0] = *(const uint4 *)(r0 + lx0);
+    xv[1] = *(const uint4 *)(r0 + lx0 + 8);
+    xv[2] = *(const uint4 *)(r1 + lx0);
+    xv[3] = *(const uint4 *)(r1 + lx0 + 8);
+    xe[0] = r0[xl];
+    xe[1] = r1[xl];
+    xe[2] = r0[xr];
+    xe[3] = r1[xr];
+    if (t < 128) {
+      const uint16_t *rt = x + (size_t)(c0 + tc) * cs + (size_t)n * HW + (size_t)min(ly0 - 1 + tr, h - 1) * w;
+      xt = *(const uint4 *)(rt + lx0 + 8 * th);
+      te2 = rt[th ? xr : xl];
     }
   };
   auto store_x = [&]() {
+    const bool ok = ly0 - 1 + r >= 0, left = lx0 > 0, right = lx0 + TT < w;
+    const uint32_t u0[8] = {xv[0].x, xv[0].y, xv[0].z, xv[0].w, xv[1].x, xv[1].y, xv[1].z, xv[1].w};
+    const uint32_t u1[8] = {xv[2].x, xv[2].y, xv[2].z, xv[2].w, xv[3].x, xv[3].y, xv[3].z, xv[3].w};
+    uint16_t *d = Xs + r * HT * XST + c;
+    *(uint32_t *)d = ok && left ? xe[0] | (xe[1] << 16) : 0u;
 #pragma unroll
-    for (int k = 0; k < NXP; ++k) {
-      const int pos = t + k * BS;
-      if (pos < HT * HT) {
+    for (int q = 0; q < 8; ++q) {
+      *(uint32_t *)(d + (2 * q + 1) * XST) = ok ? (u0[q] & 0xffffu) | (u1[q] << 16) : 0u;
+      *(uint32_t *)(d + (2 * q + 2) * XST) = ok ? (u0[q] >> 16) | (u1[q] & 0xffff0000u) : 0u;
+    }
+    *(uint32_t *)(d + (TT + 1) * XST) = ok && right ? xe[2] | (xe[3] << 16) : 0u;
+    if (t < 128) {
+      const bool okt = ly0 - 1 + tr < h;
+      uint16_t *p = Xs + (tr * HT + 8 * th + 1) * XST + tc;
+      const uint32_t v[4] = {xt.x, xt.y, xt.z, xt.w};
 #pragma unroll
-        for (int c8 = 0; c8 < CC / 8; ++c8)
-          *(uint4 *)(Xs + pos * XST + 8 * c8) = uint4{xr[k][4 * c8], xr[k][4 * c8 + 1], xr[k][4 * c8 + 2], xr[k][4 * c8 + 3]};
+      for (int q = 0; q < 4; ++q) {
+        p[2 * q * XST] = okt ? (uint16_t)v[q] : (uint16_t)0;
+        p[(2 * q + 1) * XST] = okt ? (uint16_t)(v[q] >> 16) : (uint16_t)0;
       }
+      Xs[(tr * HT + (th ? TT + 1 : 0)) * XST + tc] = okt && (th ? right : left) ? (uint16_t)te2 : (uint16_t)0;
     }
   };
   auto load_w = [&](int c0) {
@@ -374,23 +331,25 @@ __global__ void __launch_bounds__(BS) conv_fwd_mfma_pipe_kernel(int cin, int cou
       if (v < 9 * 16 * MT * 4) *(uint4 *)(Ws + (v >> 2) * WST + 8 * (v & 3)) = wr[k];
     }
   };
-  if (steps <= 0) return;
   f4 acc[MT][4];
 #pragma unroll
   for (int m = 0; m < MT; ++m)
 #pragma unroll
     for (int s = 0; s < 4; ++s) acc[m][s] = f4{0.f, 0.f, 0.f, 0.f};
   load_w(0);
-  load_x(tb, 0);
+  load_x(0);
+  const bool masked = a && mask;
+  const size_t pix0 = (size_t)n * HW + (size_t)((tile / tilesx) * TT + 4 * wave) * w + (tile % tilesx) * TT + l16;
+  uint16_t mk[2][4][4];
   for (int st = 0; st < steps; ++st) {
-    const int tile = tb + st / nch, ch = st - (st / nch) * nch;
-    if (st == 0 || nch > 1) store_w();  // one chunk: the weights stay for every tile
+    store_w();
     store_x();
     __syncthreads();
-    if (st + 1 < steps) {  // the next step's loads fly while the matrix cores work
-      const int nt = tb + (st + 1) / nch, nc = (st + 1) - ((st + 1) / nch) * nch;
-      if (nch > 1) load_w(nc * CC);
-      load_x(nt, nc * CC);
+    if (st + 1 < steps) {  // the next chunk's loads fly while the matrix cores work
+      load_w((st + 1) * CC);
+      load_x((st + 1) * CC);
+    } else if (masked) {   // a data-gradient pass's mask values, ahead of the stores
+      load_mask16(mk[0], co0, cout, kq, pix0, w, cs, mask);
     }
 #pragma unroll
     for (int tap = 0; tap < 9; ++tap) {
@@ -405,46 +364,13 @@ __global__ void __launch_bounds__(BS) conv_fwd_mfma_pipe_kernel(int cin, int cou
 #pragma unroll
         for (int s = 0; s < 4; ++s) acc[m][s] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[m], bv[s], acc[m][s], 0, 0, 0);
     }
-    if (ch == nch - 1) {  // the tile's last chunk: write it out
-      const int y0 = (tile / tilesx) * TT, x0 = (tile % tilesx) * TT;
-      const size_t pix0 = (size_t)n * HW + (size_t)(y0 + 4 * wave) * w + x0 + l16;
-#pragma unroll
-      for (int m = 0; m < MT; ++m) {
-        uint16_t mk[4][4];
-        if (a && mask) load_mask16(mk, co0 + 16 * m, cout, kq, pix0, w, cs, mask);
-        tile_out16(acc[m], mk, a && mask, co0 + 16 * m, cout, kq, pix0, w, cs, bias, z, a);
-#pragma unroll
-        for (int s = 0; s < 4; ++s) acc[m][s] = f4{0.f, 0.f, 0.f, 0.f};
-      }
-    }
-    __syncthreads();
+    if (st + 1 < steps) __syncthreads();
   }
-}
-
-// Channel-last copy of a [c][n][hw] BF16 tensor: y[(img hw + p) c + ch].
-// grid (hw / 64, c / 32, n): a workgroup moves 64 pixels x 32 channels
-// through LDS, reading rows of pixels and writing 64-byte channel runs.
-__global__ void __launch_bounds__(BS) to_nhwc_kernel(int c, int hw, const uint16_t *__restrict__ x,
-                                                     uint16_t *__restrict__ y) {
-  __shared__ uint16_t tile[32][64 + 2];
-  const int p0 = blockIdx.x * 64, c0 = blockIdx.y * 32, img = blockIdx.z, nimg = gridDim.z;
-  const int t = threadIdx.x;
-  const size_t cs = (size_t)nimg * hw;
-  {
-    const int p = t & 63, g = t >> 6;
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      const int ch = g * 8 + k;
-      tile[ch][p] = x[(size_t)(c0 + ch) * cs + (size_t)img * hw + p0 + p];
-    }
+  for (int m = 0; m < MT; ++m) {
+    if (masked && m + 1 < MT) load_mask16(mk[(m + 1) & 1], co0 + 16 * (m + 1), cout, kq, pix0, w, cs, mask);
+    tile_out16(acc[m], mk[m & 1], masked, co0 + 16 * m, cout, kq, pix0, w, cs, bias, z, a);
   }
-  __syncthreads();
-  const int p = t >> 2, part = t & 3;
-  uint32_t pk[4];
-#pragma unroll
-  for (int j = 0; j < 4; ++j)
-    pk[j] = (uint32_t)tile[part * 8 + 2 * j][p] | ((uint32_t)tile[part * 8 + 2 * j + 1][p] << 16);
-  *(uint4 *)(y + ((size_t)img * hw + p0 + p) * c + c0 + part * 8) = uint4{pk[0], pk[1], pk[2], pk[3]};
 }
 
 // The convolution for any shape with at most CP <= 384 input channels (padded to a
@@ -633,33 +559,8 @@ __global__ void __launch_bounds__(BS) conv1_fwd_kernel(int cout, int h, int w, c
   }
 }
 
-// Device buffer for the channel-last copy of a convolution input, one per
-// (device, stream) so that convolutions on different streams never share it;
-// kept until the process ends, grown (after the device has drained the work
-// that may still read it) to the largest request.
-uint16_t *nhwc_buffer(size_t elems, hipStream_t s) {
-  int dev = 0;
-  FDTD_HIP(hipGetDevice(&dev));
-  static std::mutex mu;
-  static std::map<std::pair<int, hipStream_t>, std::pair<void *, size_t>> bufs;
-  std::lock_guard<std::mutex> lock(mu);
-  auto &b = bufs[{dev, s}];
-  if (b.second < elems) {
-    if (b.first) {
-      FDTD_HIP(hipDeviceSynchronize());
-      FDTD_HIP(hipFree(b.first));
-    }
-    b.first = nullptr;
-    b.second = 0;
-    FDTD_HIP(hipMalloc(&b.first, elems * sizeof(uint16_t)));
-    b.second = elems;
-  }
-  return static_cast<uint16_t *>(b.first);
-}
-
 // One forward convolution launch: the LDS-tiled kernel where the shape and
-// the weight alignment allow it (its input staged from a channel-last copy,
-// 16-byte loads of a pixel's channels), else the one for any shape, or, beyond
+// the alignment allow it, else the one for any shape, or, beyond
 // 384 input channels, the one that stages a step at a time.
 void launch_conv(int n, int cin, int cout, int h, int w, const uint16_t *x, const uint16_t *wt, const float *bias,
                  float *z, uint16_t *a, const uint16_t *mask, hipStream_t s) {
@@ -668,25 +569,11 @@ void launch_conv(int n, int cin, int cout, int h, int w, const uint16_t *x, cons
                        z, a, mask);
     return;
   }
-  if (cin % CC == 0 && h % TT == 0 && w % TT == 0 && ((uintptr_t)wt & 15) == 0) {
-    const int tiles = (h / TT) * (w / TT), cot = cout <= 32 ? (cout + 31) / 32 : (cout + 63) / 64;
-    uint16_t *xh = nhwc_buffer((size_t)n * cin * h * w, s);
-    hipLaunchKernelGGL(to_nhwc_kernel, dim3(h * w / 64, cin / 32, n), dim3(BS), 0, s, cin, h * w, x, xh);
-    if (tiles <= 4 && cin > CC) {  // deep layers: pipelined staging, one tile per workgroup (measured)
-      const dim3 g(tiles, cot, n);
-      if (cout <= 32)
-        hipLaunchKernelGGL((conv_fwd_mfma_pipe_kernel<2>), g, dim3(BS), 0, s, cin, cout, h, w, xh, wt, bias, z,
-                           a, mask, 1);
-      else
-        hipLaunchKernelGGL((conv_fwd_mfma_pipe_kernel<4>), g, dim3(BS), 0, s, cin, cout, h, w, xh, wt, bias, z,
-                           a, mask, 1);
-      return;
-    }
-    const dim3 g(tiles, cot, n);
-    if (cout <= 32)
-      hipLaunchKernelGGL((conv_fwd_mfma_kernel<2>), g, dim3(BS), 0, s, cin, cout, h, w, xh, wt, bias, z, a, mask);
-    else
-      hipLaunchKernelGGL((conv_fwd_mfma_kernel<4>), g, dim3(BS), 0, s, cin, cout, h, w, xh, wt, bias, z, a, mask);
+  if (cin % CC == 0 && h % TT == 0 && w % TT == 0 && (((uintptr_t)wt | (uintptr_t)x) & 15) == 0) {
+    const int tiles = (h / TT) * (w / TT);
+    const dim3 g(xcd_grid((int64_t)tiles * ((cout + 16 * MT - 1) / (16 * MT)) * n));
+    auto *k = cin == CC ? &conv_fwd_mfma_kernel<true> : &conv_fwd_mfma_kernel<false>;
+    hipLaunchKernelGGL(k, g, dim3(BS), 0, s, cin, cout, h, w, x, wt, bias, z, a, mask, n);
     return;
   }
   if (cin <= 384) {  // the halo of all channels fits the LDS
