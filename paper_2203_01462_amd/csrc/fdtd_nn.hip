@@ -381,19 +381,21 @@ __global__ void __launch_bounds__(BS) conv_fwd_mfma_kernel(int cin, int cout, in
 // cin % 16 == 0 the same bits - with the weights' fragments read ahead from
 // global memory.  That kernel's time is its staging: an index division and a
 // 2-byte load per element and tap.  4 x 48 x 50 x 75 -> 80 channels:
-// 62 us -> 16.7.
+// 62 us -> 15.5.
 constexpr int GT = 8, GH = GT + 2, AHEAD = 9;  // 9 divides the steps
 
 template <int CP, bool VEC>
 __global__ void __launch_bounds__(BS) conv_gen_kernel(int cin, int cout, int h, int w, const uint16_t *__restrict__ x,
                                                      const uint16_t *__restrict__ wt, const float *__restrict__ bias,
                                                      float *__restrict__ z, uint16_t *__restrict__ a,
-                                                     const uint16_t *__restrict__ mask) {
+                                                     const uint16_t *__restrict__ mask, int nimg) {
   constexpr int S = CP + 4;  // LDS stride between pixels
   __shared__ __attribute__((aligned(16))) uint16_t Xs[GH * GH * S];
-  const int n = blockIdx.z, nimg = gridDim.z, HW = h * w, K = cin * 9;
-  const int tilesx = (w + GT - 1) / GT;
-  const int y0 = (blockIdx.x / tilesx) * GT, x0 = (blockIdx.x % tilesx) * GT, co0 = blockIdx.y * TM;
+  const int HW = h * w, K = cin * 9;
+  const int tilesx = (w + GT - 1) / GT, tiles = tilesx * ((h + GT - 1) / GT), cot = (cout + TM - 1) / TM;
+  const int item = xcd_item(blockIdx.x, gridDim.x), n = item / (cot * tiles), tile = item / cot % tiles;
+  if (n >= nimg) return;
+  const int y0 = (tile / tilesx) * GT, x0 = (tile % tilesx) * GT, co0 = item % cot * TM;
   const int t = threadIdx.x, wave = t >> 6, lane = t & 63, l16 = lane & 15, kq = lane >> 4;
   const size_t cs = (size_t)nimg * HW;
   const uint16_t *xn = x + (size_t)n * HW;
@@ -577,14 +579,14 @@ void launch_conv(int n, int cin, int cout, int h, int w, const uint16_t *x, cons
     return;
   }
   if (cin <= 384) {  // the halo of all channels fits the LDS
-    const dim3 g(((h + GT - 1) / GT) * ((w + GT - 1) / GT), (cout + TM - 1) / TM, n);
+    const dim3 g(xcd_grid((int64_t)((h + GT - 1) / GT) * ((w + GT - 1) / GT) * ((cout + TM - 1) / TM) * n));
     auto pick = [&](auto vec) {
       constexpr bool V = decltype(vec)::value;
       return cin <= 64 ? &conv_gen_kernel<64, V> : cin <= 128 ? &conv_gen_kernel<128, V>
              : cin <= 256 ? &conv_gen_kernel<256, V> : &conv_gen_kernel<384, V>;
     };
     auto *k = cin % 4 == 0 && ((uintptr_t)wt & 7) == 0 ? pick(std::true_type()) : pick(std::false_type());
-    hipLaunchKernelGGL(k, g, dim3(BS), 0, s, cin, cout, h, w, x, wt, bias, z, a, mask);
+    hipLaunchKernelGGL(k, g, dim3(BS), 0, s, cin, cout, h, w, x, wt, bias, z, a, mask, n);
     return;
   }
   const dim3 g((h * w + TN - 1) / TN, (cout + TM - 1) / TM, n);
@@ -605,7 +607,10 @@ void launch_conv(int n, int cin, int cout, int h, int w, const uint16_t *x, cons
 // channels): output channels 16(w & 1).. and input half w >> 1 (1 x 9).
 // With bpart, the workgroups of the first input chunk also write the
 // split's bias partial sums bpart[split * stride + co] = sum of dz[co][q]
-// over its tiles.  grid (ceil(cout/CT), cin/32, splits).
+// over its tiles.  One-dimensional grid of xcd_grid(ceil(cout/CT) * ceil(cin/32) *
+// splits): with the items of neighbouring tiles on one XCD, 96 -> 32 channels on 32
+// images of 128^2 takes 101 us (146 when they went round-robin), 64 -> 64 at 64^2
+// 36 (46).
 // RAG: any shape and alignment: tiles and channels may hang over (zeros there),
 // rows are loaded by raw8, and the bias sums are kept in FP64.  The
 // kernel it replaces formed an index by division per element and matrix step:
@@ -619,19 +624,24 @@ __global__ void __launch_bounds__(BS) conv_wgrad_mfma_kernel(int nimg, int cin, 
                                                             const uint16_t *__restrict__ x,
                                                             const uint16_t *__restrict__ dz,
                                                             float *__restrict__ part, int64_t stride,
-                                                            int tiles_per_split, float *__restrict__ bpart) {
+                                                            int tiles_per_split, float *__restrict__ bpart,
+                                                            int splits) {
   constexpr int NT = CT / 32;           // 16-channel input halves per wavefront
   constexpr int DV = CT * GY * 2 / BS;  // 16-byte dz vectors per thread and tile
   __shared__ __attribute__((aligned(16))) uint16_t Ds[CT * DST];
   __shared__ __attribute__((aligned(16))) uint16_t Xs[3 * 32 * XCI];
   const int HW = h * w;
   const size_t P = (size_t)nimg * HW;
-  const int co0 = blockIdx.x * CT, ci0 = blockIdx.y * 32, split = blockIdx.z;
+  // items: output blocks fastest, then input chunks, then splits (neighbours read
+  // the same tiles)
+  const int gx = (cout + CT - 1) / CT, gy = (cin + 31) / 32, item = xcd_item(blockIdx.x, gridDim.x);
+  const int co0 = item % gx * CT, ci0 = item / gx % gy * 32, split = item / (gx * gy);
+  if (split >= splits) return;
   const int tx_n = (w + GX - 1) / GX, tiles_img = ((h + GY - 1) / GY) * tx_n, tiles = nimg * tiles_img;
   const int T0 = split * tiles_per_split, T1 = min(tiles, T0 + tiles_per_split);
   const int t = threadIdx.x, wave = t >> 6, lane = t & 63, l16 = lane & 15, kq = lane >> 4;
   const int cw = CT == 64 ? wave : (wave & 1), nb = CT == 64 ? 0 : (wave >> 1);
-  const bool with_bias = bpart != nullptr && blockIdx.y == 0;
+  const bool with_bias = bpart != nullptr && ci0 == 0;
   f4 acc[NT][9];
 #pragma unroll
   for (int nt = 0; nt < NT; ++nt)
@@ -1361,10 +1371,11 @@ void wgrad_run(int32_t n, int32_t cin, int32_t cout, int32_t h, int32_t w, const
       // (whole tiles at odd addresses are loaded element by element, like ragged ones)
       const bool vec = pl.tiled && ((uintptr_t)dz & 15) == 0 && ((uintptr_t)x & 15) == 0;
       const int ct = wgrad_ct(cout);
-      const dim3 g((cout + ct - 1) / ct, (cin + 31) / 32, pl.splits);
+      const dim3 g(xcd_grid((int64_t)((cout + ct - 1) / ct) * ((cin + 31) / 32) * pl.splits));
       auto *k = ct == 32 ? (vec ? &conv_wgrad_mfma_kernel<32, false> : &conv_wgrad_mfma_kernel<32, true>)
                          : (vec ? &conv_wgrad_mfma_kernel<64, false> : &conv_wgrad_mfma_kernel<64, true>);
-      hipLaunchKernelGGL(k, g, dim3(BS), 0, s, n, cin, cout, h, w, x, dz, work, stride, pl.chunk, bp);
+      hipLaunchKernelGGL(k, g, dim3(BS), 0, s, n, cin, cout, h, w, x, dz, work, stride, pl.chunk, bp,
+                         pl.splits);
     }
     if (db && db == dw + m) {  // contiguous weight and bias gradients: one reduction
       launch_split_sum(work, pl.splits, stride, m + cout, dw, s);
