@@ -119,6 +119,11 @@ fdtd_status fdtd_nn_from_bf16(int64_t count, const uint16_t *x, float *y, void *
  * (FP32 gradients); 2x nearest upsampling of planes h x w and its transpose. */
 fdtd_status fdtd_nn_pool2(int64_t planes, int32_t h, int32_t w, const uint16_t *x, uint16_t *y, void *stream);
 fdtd_status fdtd_nn_pool2_backward(int64_t planes, int32_t h, int32_t w, const float *dy, float *dx, void *stream);
+/* Where a pooled activation a (a ReLU output) also feeds a skip connection:
+ * dz = bf16((dx + skip) * (a > 0)), dx the transpose of the pooling of dy; the same
+ * values as pool2_backward, axpy and relu_bf16_backward one after another. */
+fdtd_status fdtd_nn_pool2_backward_join(int64_t planes, int32_t h, int32_t w, const float *dy, const float *skip,
+                                        const uint16_t *a, uint16_t *dz, void *stream);
 fdtd_status fdtd_nn_up2(int64_t planes, int32_t h, int32_t w, const uint16_t *x, uint16_t *y, void *stream);
 fdtd_status fdtd_nn_up2_backward(int64_t planes, int32_t h, int32_t w, const float *dy, float *dx, void *stream);
 

@@ -1061,6 +1061,42 @@ __global__ void __launch_bounds__(BS) pool2_back_kernel(int64_t planes, int h, i
   dx[i] = 0.25f * dy[(size_t)pl * (h / 2) * (w / 2) + (size_t)(yi / 2) * (w / 2) + xi / 2];
 }
 
+// The gradients that meet at a pooled and skipped activation a, through its ReLU:
+// dz = bf16((0.25 dy[plane][i/2][j/2] + skip[plane][i][j]) * (a > 0)), the values of
+// pool2_back, axpy and relu_back one after another.  V elements of a row per thread
+// (8: 16-byte accesses; w % 8 == 0, aligned).  What bounds it is its bytes: the
+// three levels of 32 images of 128^2 took 119 us as three passes each, 49 in one.
+template <int V>
+__global__ void __launch_bounds__(BS) pool2_back_join_kernel(int64_t planes, int h, int w, const float *__restrict__ dy,
+                                                            const float *__restrict__ skip,
+                                                            const uint16_t *__restrict__ a,
+                                                            uint16_t *__restrict__ dz) {
+  const int wv = w / V;
+  const int64_t i = (int64_t)blockIdx.x * BS + threadIdx.x;
+  if (i >= planes * h * wv) return;
+  const int64_t pl = i / ((int64_t)h * wv);
+  const int r = (int)(i % ((int64_t)h * wv)), yi = r / wv, xi = V * (r - yi * wv);
+  const float *g = dy + (size_t)pl * (h / 2) * (w / 2) + (size_t)(yi / 2) * (w / 2) + xi / 2;
+  const size_t o = (size_t)pl * h * w + (size_t)yi * w + xi;
+  if constexpr (V == 8) {
+    const float4 q = *(const float4 *)g, s0 = *(const float4 *)(skip + o), s1 = *(const float4 *)(skip + o + 4);
+    const uint4 av = *(const uint4 *)(a + o);
+    const uint32_t aw[4] = {av.x, av.y, av.z, av.w};
+    const float gv[4] = {q.x, q.y, q.z, q.w}, sv[8] = {s0.x, s0.y, s0.z, s0.w, s1.x, s1.y, s1.z, s1.w};
+    uint32_t u[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const float p = 0.25f * gv[k];
+      const uint16_t lo = f2bf(bf2f((uint16_t)(aw[k] & 0xffffu)) > 0.f ? __fadd_rn(p, sv[2 * k]) : 0.f);
+      const uint16_t hi = f2bf(bf2f((uint16_t)(aw[k] >> 16)) > 0.f ? __fadd_rn(p, sv[2 * k + 1]) : 0.f);
+      u[k] = (uint32_t)lo | ((uint32_t)hi << 16);
+    }
+    *(uint4 *)(dz + o) = uint4{u[0], u[1], u[2], u[3]};
+  } else {
+    dz[o] = f2bf(bf2f(a[o]) > 0.f ? __fadd_rn(0.25f * g[0], skip[o]) : 0.f);
+  }
+}
+
 // y[plane][2i+a][2j+b] = x[plane][i][j]
 __global__ void __launch_bounds__(BS) up2_kernel(int64_t planes, int h, int w, const uint16_t *__restrict__ x,
                                                 uint16_t *__restrict__ y) {
@@ -1471,6 +1507,21 @@ fdtd_status fdtd_nn_pool2_backward(int64_t planes, int32_t h, int32_t w, const f
     else
       hipLaunchKernelGGL(pool2_back_kernel, dim3(nb_of(planes * h * w)), dim3(BS), 0, (hipStream_t)stream, planes, h,
                          w, dy, dx);
+    FDTD_HIP(hipGetLastError());
+  });
+}
+
+fdtd_status fdtd_nn_pool2_backward_join(int64_t planes, int32_t h, int32_t w, const float *dy, const float *skip,
+                                        const uint16_t *a, uint16_t *dz, void *stream) {
+  return nguard([&] {
+    need(planes > 0 && h > 1 && w > 1 && h % 2 == 0 && w % 2 == 0 && dy && skip && a && dz);
+    hipStream_t s = (hipStream_t)stream;
+    if (w % 8 == 0 && aligned(dy, 16) && aligned(skip, 16) && aligned(a, 16) && aligned(dz, 16))
+      hipLaunchKernelGGL(pool2_back_join_kernel<8>, dim3(nb_of(planes * h * (w / 8))), dim3(BS), 0, s, planes, h, w, dy,
+                         skip, a, dz);
+    else
+      hipLaunchKernelGGL(pool2_back_join_kernel<1>, dim3(nb_of(planes * h * w)), dim3(BS), 0, s, planes, h, w, dy, skip,
+                         a, dz);
     FDTD_HIP(hipGetLastError());
   });
 }

@@ -80,7 +80,7 @@ EXPORTS = ["fdtd_abi_version", "fdtd_create", "fdtd_set_density", "fdtd_forward"
            "fdtd_nn_wgrad_work",
            "fdtd_nn_conv3x3_wgrad", "fdtd_nn_conv3x3_wgrad_noalloc",
            "fdtd_nn_relu_bf16", "fdtd_nn_relu_bf16_backward", "fdtd_nn_to_bf16", "fdtd_nn_from_bf16",
-           "fdtd_nn_pool2", "fdtd_nn_pool2_backward", "fdtd_nn_up2", "fdtd_nn_up2_backward", "fdtd_nn_adam",
+           "fdtd_nn_pool2", "fdtd_nn_pool2_backward", "fdtd_nn_pool2_backward_join", "fdtd_nn_up2", "fdtd_nn_up2_backward", "fdtd_nn_adam",
            "fdtd_nn_axpy", "fdtd_nn_gap_linear", "fdtd_nn_gap_linear_backward", "fdtd_nn_mse_work", "fdtd_nn_mse",
            "fdtd_nn_last_error"]
 
@@ -154,6 +154,7 @@ def load_library(path=LIB_PATH):
         "fdtd_nn_from_bf16": [I64, P, P, P],
         "fdtd_nn_pool2": [I64, I32, I32, P, P, P],
         "fdtd_nn_pool2_backward": [I64, I32, I32, P, P, P],
+        "fdtd_nn_pool2_backward_join": [I64, I32, I32, P, P, P, P, P],
         "fdtd_nn_up2": [I64, I32, I32, P, P, P],
         "fdtd_nn_up2_backward": [I64, I32, I32, P, P, P],
         "fdtd_nn_adam": [I64, P, P, P, P, P, F, F, F, F, I32, P],

@@ -124,6 +124,13 @@ def pool2_backward(dy, dx, planes, h, w, stream=None):
     _check(load_library().fdtd_nn_pool2_backward(planes, h, w, _p(dy), _p(dx), _s(stream)))
 
 
+def pool2_backward_join(dy, skip, a, dz, planes, h, w, stream=None):
+    """The gradients that meet at a pooled and skipped activation a, through its
+    ReLU: dz = bf16((pool2_backward(dy) + skip) * (a > 0))."""
+    _check(load_library().fdtd_nn_pool2_backward_join(planes, h, w, _p(dy), _p(skip), _p(_u16(a)), _p(_u16(dz)),
+                                                      _s(stream)))
+
+
 def up2(x, y, planes, h, w, stream=None):
     _check(load_library().fdtd_nn_up2(planes, h, w, _p(_u16(x)), _p(_u16(y)), _s(stream)))
 
@@ -320,8 +327,8 @@ class UNet:
         its BF16 pre-activation gradient gz when the layer above formed it.
         Writes the FP32 input gradient into gx unless gx is None; with fuse
         (x is the ReLU output of the layer below, whose backward comes next)
-        writes that layer's BF16 pre-activation gradient into self.gz2 instead
-        and returns it."""
+        writes that layer's BF16 pre-activation gradient into the one of self.gz
+        and self.gz2 that gz is not in and returns it."""
         cin, cout, _ = self.plan[li]
         n, st = self.n, self.stream
         cnt = cout * n * h * h
@@ -333,7 +340,8 @@ class UNet:
                 relu_bf16_backward(a_out, ga[:cnt], gz, stream=st)
         conv3x3_wgrad(x, gz, self.dw(li), self.db(li), self.work, n, cin, cout, h, h, stream=st)
         if fuse:
-            out = self.gz2[:cin * n * h * h]
+            other = self.gz if gz.data_ptr() == self.gz2.data_ptr() else self.gz2
+            out = other[:cin * n * h * h]
             conv3x3_dgrad_relu(gz, None, self.wrot_of(li), x, out, n, cin, cout, h, h, stream=st)
             return out
         if gx is not None:
@@ -351,13 +359,13 @@ class UNet:
                         stream=st)
             self._rot_ok = True
         # sensitivity head and decoder, top down
-        self._conv_back(li, self.d2[0], None, dS, ga, s)
+        gz = self._conv_back(li, self.d2[0], None, dS, None, s, fuse=True)
         for l in range(L - 1):
             sz = s >> l
             li -= 1
-            gz = self._conv_back(li, self.d1[l], self.d2[l], ga, None, sz, fuse=True)
+            gz = self._conv_back(li, self.d1[l], self.d2[l], ga, None, sz, gz=gz, fuse=True)
             li -= 1
-            self._conv_back(li, self.cat[l], self.d1[l], None, self.gcat[l], sz, gz=gz)
+            gz = self._conv_back(li, self.cat[l], self.d1[l], None, self.gcat[l], sz, gz=gz)
             # up half of the concat gradient -> gradient of the level below's output
             up_cnt = ch[l + 1] * n * sz * sz
             up2_backward(self.gcat[l][:up_cnt], ga[:up_cnt // 4], ch[l + 1] * n, sz // 2, sz // 2, stream=st)
@@ -372,14 +380,13 @@ class UNet:
         for l in range(L - 1, -1, -1):
             sz = s >> l
             li = 2 * l + 1
+            gz = None
             if l < L - 1:
-                # ga holds the gradient of pooled[l]; expand it and add the skip gradient
-                pool2_backward(ga[:ch[l] * n * (sz // 2) ** 2], gb[:ch[l] * n * sz * sz], ch[l] * n, sz, sz,
-                               stream=st)
-                up_cnt = ch[l + 1] * n * sz * sz
-                axpy(1.0, self.gcat[l][up_cnt:], gb[:ch[l] * n * sz * sz], stream=st)
-                ga, gb = gb, ga
-            gz = self._conv_back(li, self.e1[l], self._skip(l), ga, None, sz, fuse=True)
+                # ga holds the gradient of pooled[l]; the skip gradient joins it
+                gz = self.gz[:ch[l] * n * sz * sz]
+                pool2_backward_join(ga[:ch[l] * n * (sz // 2) ** 2], self.gcat[l][ch[l + 1] * n * sz * sz:],
+                                    self._skip(l), gz, ch[l] * n, sz, sz, stream=st)
+            gz = self._conv_back(li, self.e1[l], self._skip(l), ga, None, sz, gz=gz, fuse=True)
             x = self.x0 if l == 0 else self.pooled[l - 1]
             self._conv_back(li - 1, x, self.e1[l], None, None if l == 0 else ga, sz, gz=gz)
 

@@ -71,3 +71,21 @@ def test_odd_addresses(nn, n, cin, cout, h, w):  # noqa: F811
         out.append((z.cpu(), dw.cpu()))
     assert torch.equal(out[0][0], out[1][0])
     assert torch.equal(out[0][1], out[1][1])
+
+
+@pytest.mark.parametrize("planes,h,w", [(1, 2, 2), (3, 6, 10), (5, 16, 24), (64, 32, 32)])
+def test_pool_backward_join(nn, planes, h, w):  # noqa: F811
+    """The joined gradient of a pooled and skipped activation against the three
+    calls it replaces, bit for bit (the element-wise and the 16-byte kernels)."""
+    g = torch.Generator().manual_seed(h + w)
+    dy = torch.randn(planes * h * w // 4, generator=g).cuda()
+    skip = torch.randn(planes * h * w, generator=g).cuda()
+    a = T.bits(torch.relu(torch.randn(planes * h * w, generator=g)))
+    dx, want = torch.empty_like(skip), torch.empty_like(a)
+    nn.pool2_backward(dy, dx, planes, h, w)
+    nn.axpy(1.0, skip, dx)
+    nn.relu_bf16_backward(a, dx, want)
+    got = torch.full_like(a, 0x7fff)
+    nn.pool2_backward_join(dy, skip, a, got, planes, h, w)
+    torch.cuda.synchronize()
+    assert torch.equal(got.cpu(), want.cpu())
