@@ -36,11 +36,29 @@ HBM_PEAK_GBS = 8000.0
 # the sources they were taken on: the kernels and the library code that
 # orders their workgroups.  Reported only while those sources are unchanged;
 # the summaries live in profiles/.
-SRC_2D = ["paper_2203_01462_amd/csrc/fdtd_2d_multi.hip", "paper_2203_01462_amd/csrc/fdtd_api.hip"]
+SRC_2D = ["paper_2203_01462_amd/csrc/fdtd_2d_multi.hip", "paper_2203_01462_amd/csrc/fdtd_multi.hpp", "paper_2203_01462_amd/csrc/fdtd_api.hip"]
 SRC_BATCH = ["paper_2203_01462_amd/csrc/fdtd_2d.hip", "paper_2203_01462_amd/csrc/fdtd_api.hip"]
 SRC_3D = ["paper_2203_01462_amd/csrc/fdtd_3d.hip", "paper_2203_01462_amd/csrc/fdtd_api.hip"]
-SRC_TE = ["paper_2203_01462_amd/csrc/fdtd_te_multi.hip", "paper_2203_01462_amd/csrc/fdtd_api.hip"]
-MEASURED_TRAFFIC = {}
+SRC_TE = ["paper_2203_01462_amd/csrc/fdtd_te_multi.hip", "paper_2203_01462_amd/csrc/fdtd_multi.hpp", "paper_2203_01462_amd/csrc/fdtd_api.hip"]
+MEASURED_TRAFFIC = {
+    # one launch = eight time steps of the grid
+    "tmz2d_2048_fp32": {"sources": SRC_2D, "sha256_16": "287c30f0d43921b2",
+                        "fwd": 26.5e6, "adj": 29.4e6,
+                        "profile": "profiles/step2d_multi_tmz2d_2048_fp32.md"},
+    # one time step of all 64 instances = one step2d_batch_mix_kernel launch
+    "tmz2d_batch64_c4": {"sources": SRC_BATCH, "sha256_16": "62afda7100bc1403",
+                         "fwd": 501.0e6, "adj": 522.7e6,
+                         "profile": "profiles/step2d_batch_mix_kernel_tmz2d_batch64_c4.md"},
+    # one time step = the general update (forward: one step3d_general_fwd
+    # launch; adjoint: three step3d_general launches) + step3d_plain
+    "yee3d_256_fp32": {"sources": SRC_3D, "sha256_16": "8c990233c744e197",
+                       "fwd": 1303.8e6, "adj": 1337.3e6,
+                       "profile": "profiles/step3d_yee3d_256_fp32.md"},
+    # one launch = eight time steps of the grid
+    "te2d_2048_fp32": {"sources": SRC_TE, "sha256_16": "a6b04f701f78df53",
+                       "fwd": 40.7e6, "adj": 50.9e6,
+                       "profile": "profiles/step_te_multi_te2d_2048_fp32.md"},
+}
 
 
 def sources_sha(paths):
