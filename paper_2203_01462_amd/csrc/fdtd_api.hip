@@ -299,6 +299,15 @@ void create_2d(fdtd_ctx *c, Kind2D kind) {
   c->nmon = c->ng;
   c->jref = c->ja - 2;
   c->L = c->jb + 2 - c->jref + 1;
+  if (!tf && c->L >= 0) {
+    // Without a plane wave the total-field box need not exist, and its lines could
+    // lie anywhere in their tables or outside them.  The several-step kernels give a
+    // design region at the absorber the body that reads the tables, so the lines go
+    // where no region reaches and the tables hold the rows that body reads: zeros.
+    c->ia = c->ib = c->ja = c->jb = -4096;
+    c->jref = c->ja - 1;
+    c->L = 2;
+  }
   const size_t n2 = (size_t)c->pitch * c->ny * c->esz;
   for (int b = 0; b < 2; ++b) {
     for (int k = 0; k < 3; ++k) c->fld[b][k].alloc(n2);
