@@ -326,6 +326,12 @@ void create_2d(fdtd_ctx *c, Kind2D kind) {
   c->super_tiles = (int)pl.tb.size();
   // (the several-step kernel indexes a field with 32 bits)
   c->multi = kind == Kind2D::kMulti && blocking_enabled(2) && (int64_t)c->pitch * c->ny < INT32_MAX;
+  // (... and updates every design and gap edge: TEz boxes that reach a PEC wall, which
+  // they may without an absorber and a plane wave, hold edges that are never updated)
+  auto on_wall = [&](const int32_t *lo, const int32_t *n) {
+    return lo[0] == 0 || lo[1] == 0 || lo[0] + n[0] == c->nx - 1 || lo[1] + n[1] == c->ny - 1;
+  };
+  if (c->te && (on_wall(g.design_lo, g.design_n) || (c->ng > 0 && on_wall(g.gap_lo, g.gap_n)))) c->multi = false;
   if (c->multi) {
     const int n2d[1][2] = {{c->nx, c->ny}};
     c->mt = c->te ? multi_te_tile(c->nx, c->ny, c->prec) : multi2d_tile(n2d, 1, c->prec);

@@ -26,8 +26,8 @@
 // design or gap box take one row per wavefront and a body with the design
 // and gap code; all other blocks a body without it.  Every array a halo
 // reads has a read and a write copy.  Contexts take several steps per launch
-// (fdtd_te_multi.hip) unless that is switched off or a field exceeds 32-bit
-// indices; this kernel remains for those.
+// (fdtd_te_multi.hip) unless that is switched off, a field exceeds 32-bit
+// indices or a box reaches a PEC wall; this kernel remains for those.
 
 // Design layout (per edge): the design box of dnx x dny cells holds its E_x
 // edges [dny+1][dnx] (density indices 0 .. ndx-1) followed by its E_y edges

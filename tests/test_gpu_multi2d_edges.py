@@ -1,6 +1,7 @@
 """Several time steps per launch (2D TMz and TEz) without a plane wave, against the
 per-step kernels from a random state: total-field boxes that do not exist (incident
-tables of 0, 1 and 2 entries) under regions that hold design and absorber nodes.
+tables of 0, 1 and 2 entries) under regions that hold design and absorber nodes, and
+TEz boxes that reach the walls.
 TMz in FP64 to the last bit, TEz in FP64 to 1e-11 (the bar against the oracle);
 FP32 1e-4 on F and the state, 1e-3 on the gradient."""
 import numpy as np
@@ -45,3 +46,15 @@ def test_no_plane_wave_needs_no_incident_tables(gpu, prec, te, ny, margin, entri
            gap_lo=(55, 12, 0), gap_n=(2, 2, 1), pml_kappa_max=2.0)
     say(f"[multi2d] no plane wave, {'TEz' if te else 'TMz'} fp{prec} {nx}x{ny} margin {margin}")
     both_paths(gpu, w, prec == 64 and not te)
+
+
+@pytest.mark.parametrize("prec", [64, 32])
+@pytest.mark.parametrize("nx,ny,gap", [(40, 37, (0, 12)), (40, 37, (37, 34)), (130, 70, (60, 0)), (130, 70, (60, 30))])
+def test_te_design_and_gap_up_to_the_walls(gpu, prec, nx, ny, gap):
+    """TEz without an absorber and without a plane wave: the design box may reach the
+    PEC walls, and the gap too.  Their edges on the walls keep E = 0 (and the
+    current they were given) and have no gradient."""
+    w = W.tiny_te(precision=prec, n=(nx, ny, 1), pml_cells=0, tfsf_margin=0, source="none", weights="unit", n_steps=43,
+                  design_lo=(0, 0, 0), design_n=(nx - 1, ny - 1, 1), gap_lo=gap + (0,), gap_n=(2, 2, 1))
+    say(f"[multi2d] TEz design up to the walls fp{prec} {nx}x{ny} gap {gap}")
+    both_paths(gpu, w, False)
