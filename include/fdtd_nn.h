@@ -85,8 +85,9 @@ fdtd_status fdtd_nn_rot_weights(int32_t nlayers, const int32_t *cin, const int32
                                 const uint16_t *w, uint16_t *wrot, void *stream);
 
 /* dw[co][ky][kx][ci] = sum_{n,y,x} dz[co][n][y][x] x[ci][n][y+ky-1][x+kx-1];
- * db[co] = sum_{n,y,x} dz; work: caller workspace of fdtd_nn_wgrad_work(...)
- * floats. */
+ * db[co] = sum_{n,y,x} dz (in images that do not fill the 8 x 16-pixel tiles, or
+ * tensors off a 16-byte address: summed in FP64 and rounded once); work: caller
+ * workspace of fdtd_nn_wgrad_work(...) floats. */
 int64_t fdtd_nn_wgrad_work(int32_t n, int32_t cin, int32_t cout, int32_t h, int32_t w);
 fdtd_status fdtd_nn_conv3x3_wgrad(int32_t n, int32_t cin, int32_t cout, int32_t h, int32_t w, const uint16_t *x,
                                   const uint16_t *dz, float *dw, float *db, float *work, void *stream);
@@ -95,10 +96,10 @@ fdtd_status fdtd_nn_conv3x3_wgrad(int32_t n, int32_t cin, int32_t cout, int32_t 
  * capture, tight serving loops, harnesses that forbid hipMalloc): the same
  * dw and db as fdtd_nn_conv3x3_wgrad, bit for bit (same kernels and split
  * plan), with the partial sums in a scratch array the library holds on each
- * device (64 MiB = 16 Mi floats, kept until the process ends) instead of a
+ * device (72 MiB = 18 Mi floats, kept until the process ends) instead of a
  * caller workspace.  Allocates nothing and calls no allocating routine; the
  * device is the current one.  EINVAL when fdtd_nn_wgrad_work(...) exceeds
- * 16 Mi floats (every layer of the surrogate fits: the plan's largest
+ * 18 Mi floats (every layer of the surrogate fits: the plan's largest
  * workspace is about 14.2 Mi floats).  Calls on one device share the array:
  * calls that overlap on one GPU (different streams or threads) race and
  * must be serialized by the caller. */

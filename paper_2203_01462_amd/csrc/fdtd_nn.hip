@@ -606,13 +606,14 @@ void launch_conv(int n, int cin, int cout, int h, int w, const uint16_t *x, cons
 // (2 x 9 accumulator tiles); CT = 32 (layers with at most 32 output
 // channels): output channels 16(w & 1).. and input half w >> 1 (1 x 9).
 // With bpart, the workgroups of the first input chunk also write the
-// split's bias partial sums bpart[split * stride + co] = sum of dz[co][q]
-// over its tiles.  One-dimensional grid of xcd_grid(ceil(cout/CT) * ceil(cin/32) *
+// split's bias partial sums: the sum of dz[co][q] over its tiles, as float
+// bpart[split * stride + co], with RAG as double bpart[split * cout + co].  One-dimensional grid of xcd_grid(ceil(cout/CT) * ceil(cin/32) *
 // splits): with the items of neighbouring tiles on one XCD, 96 -> 32 channels on 32
 // images of 128^2 takes 101 us (146 when they went round-robin), 64 -> 64 at 64^2
 // 36 (46).
 // RAG: any shape and alignment: tiles and channels may hang over (zeros there),
-// rows are loaded by raw8, and the bias sums are kept in FP64.  The
+// rows are loaded by raw8, and the bias sums stay in FP64 until all of them are
+// added.  The
 // kernel it replaces formed an index by division per element and matrix step:
 // 4 x (48 -> 80) x 50 x 75 46 us -> 19.
 constexpr int GY = 8, GX = 16, GP = GY * GX;  // pixel tile
@@ -624,7 +625,7 @@ __global__ void __launch_bounds__(BS) conv_wgrad_mfma_kernel(int nimg, int cin, 
                                                             const uint16_t *__restrict__ x,
                                                             const uint16_t *__restrict__ dz,
                                                             float *__restrict__ part, int64_t stride,
-                                                            int tiles_per_split, float *__restrict__ bpart,
+                                                            int tiles_per_split, void *__restrict__ bpart,
                                                             int splits) {
   constexpr int NT = CT / 32;           // 16-channel input halves per wavefront
   constexpr int DV = CT * GY * 2 / BS;  // 16-byte dz vectors per thread and tile
@@ -790,7 +791,9 @@ __global__ void __launch_bounds__(BS) conv_wgrad_mfma_kernel(int nimg, int cin, 
 #pragma unroll
       for (int o = 8; o > 0; o >>= 1) v += __shfl_xor(v, o, 16);
       const int co = co0 + (t >> 4) + 16 * k;
-      if ((t & 15) == 0 && co < cout) bpart[(size_t)split * stride + co] = (float)v;
+      if ((t & 15) != 0 || co >= cout) continue;
+      if (!RAG) ((float *)bpart)[(size_t)split * stride + co] = (float)v;
+      else ((double *)bpart)[(size_t)split * cout + co] = v;
     }
   }
 }
@@ -894,8 +897,8 @@ struct WgradPlan {
 // Output-channel tile of the tiled weight gradient.
 inline int wgrad_ct(int cout) { return cout <= 32 ? 32 : 64; }
 
-// The splits that the workspace of a ragged shape has room for: 768 workgroups of
-// 64 x 64 weights, at least 256 pixels each.
+// The most splits a ragged shape takes: 768 workgroups of 64 x 64 weights, at least
+// 256 pixels each (fewer partial sums than that per pixel cost more than they give).
 int wgrad_splits(int n, int cin, int cout, int h, int w) {
   const int64_t P = (int64_t)n * h * w;
   const int64_t groups = (int64_t)((cin * 9 + TN - 1) / TN) * ((cout + TM - 1) / TM);
@@ -938,9 +941,6 @@ WgradPlan wgrad_plan(int n, int cin, int cout, int h, int w) {
   return pl;
 }
 
-// Bias sums that the workspace of a ragged shape has room for, beside its splits.
-int64_t bias_ranges(int64_t P) { return std::min<int64_t>(64, std::max<int64_t>(1, (P + 16383) / 16384)); }
-
 // out[i] = sum over k < splits of part[k * stride + i], i < m.  G groups of
 // consecutive splits per output, each summed in split order (the unrolled
 // loads are issued ahead; the additions keep their order), then the G group
@@ -948,8 +948,8 @@ int64_t bias_ranges(int64_t P) { return std::min<int64_t>(64, std::max<int64_t>(
 // wavefronts' loads in flight per output row when the splits are many.
 // grid ceil(m / 64), 64 G threads.
 template <int G>
-__global__ void __launch_bounds__(64 * G) split_sum_kernel(const float *__restrict__ part, int splits, int64_t stride,
-                                                          int64_t m, float *__restrict__ out) {
+__device__ __forceinline__ void split_sum(const float *__restrict__ part, int splits, int64_t stride, int64_t m,
+                                          float *__restrict__ out) {
   __shared__ float red[G][64];
   const int o = threadIdx.x & 63, g = threadIdx.x >> 6;
   const int64_t i = (int64_t)blockIdx.x * 64 + o;
@@ -971,6 +971,54 @@ __global__ void __launch_bounds__(64 * G) split_sum_kernel(const float *__restri
       out[i] = r;
     }
   }
+}
+
+template <int G>
+__global__ void __launch_bounds__(64 * G) split_sum_kernel(const float *__restrict__ part, int splits, int64_t stride,
+                                                          int64_t m, float *__restrict__ out) {
+  split_sum<G>(part, splits, stride, m, out);
+}
+
+// The same with the bias sums db[co] of bpart[split][cout], in FP64 up to their one
+// rounding, in the blocks after the weights': 64 channels a block or, of a layer with
+// fewer, the next power of two, the threads left over taking more groups of splits
+// (pairwise sums of the groups: a fixed order).
+template <int G>
+__global__ void __launch_bounds__(64 * G) split_sum2_kernel(const float *__restrict__ part, int splits, int64_t m,
+                                                           float *__restrict__ dw, const double *__restrict__ bpart,
+                                                           int cout, float *__restrict__ db) {
+  const int nb = (int)((m + 63) / 64), b = (int)blockIdx.x - nb;
+  if (b < 0) {
+    split_sum<G>(part, splits, m, m, dw);
+    return;
+  }
+  __shared__ double red[64 * G];
+  int cp = 64;
+  while (cp / 2 >= cout) cp /= 2;
+  const int t = threadIdx.x, co = 64 * b + (t & (cp - 1)), g = t / cp, ng = 64 * G / cp;
+  const int k0 = (int)((int64_t)splits * g / ng), k1 = (int)((int64_t)splits * (g + 1) / ng);
+  double s = 0;
+  if (co < cout) {
+#pragma unroll 8
+    for (int k = k0; k < k1; ++k) s += bpart[(size_t)k * cout + co];
+  }
+  red[t] = s;
+  for (int w = 32 * G; w >= cp; w >>= 1) {
+    __syncthreads();
+    if (t < w) red[t] += red[t + w];
+  }
+  if (t < cp && co < cout) db[co] = (float)red[t];
+}
+
+void launch_split_sum2(const float *part, int splits, int64_t m, float *dw, const double *bpart, int cout, float *db,
+                       hipStream_t s) {
+  const dim3 g((unsigned)((m + 63) / 64 + (cout + 63) / 64));
+  if (splits >= 64)
+    hipLaunchKernelGGL(split_sum2_kernel<16>, g, dim3(64 * 16), 0, s, part, splits, m, dw, bpart, cout, db);
+  else if (splits >= 16)
+    hipLaunchKernelGGL(split_sum2_kernel<4>, g, dim3(64 * 4), 0, s, part, splits, m, dw, bpart, cout, db);
+  else
+    hipLaunchKernelGGL(split_sum2_kernel<1>, g, dim3(64), 0, s, part, splits, m, dw, bpart, cout, db);
 }
 
 void launch_split_sum(const float *part, int splits, int64_t stride, int64_t m, float *out, hipStream_t s) {
@@ -1377,20 +1425,20 @@ fdtd_status fdtd_nn_rot_weights(int32_t nlayers, const int32_t *cin, const int32
 int64_t fdtd_nn_wgrad_work(int32_t n, int32_t cin, int32_t cout, int32_t h, int32_t w) {
   if (n <= 0 || cin <= 0 || cout <= 0 || h <= 0 || w <= 0) return 0;
   const WgradPlan pl = wgrad_plan(n, cin, cout, h, w);
-  const int64_t P = (int64_t)n * h * w, splits = pl.c1 || pl.tiled ? pl.splits : wgrad_splits(n, cin, cout, h, w);
-  // splits rows of cout * cin * 9 weight and cout bias sums (a ragged shape's may
-  // be fewer)
-  return splits * cout * cin * 9 + std::max(splits, bias_ranges(P)) * cout;
+  // splits rows of cout * cin * 9 weight and cout bias sums, the latter FP64 (and
+  // 8-byte aligned) in the kernel for any shape and alignment
+  const int64_t m = (int64_t)cout * cin * 9;
+  return pl.c1 ? pl.splits * (m + cout) : pl.splits * (m + 2 * cout) + 1;
 }
 
 }  // extern "C"
 
 // Scratch of the allocation-free weight gradient: one array per device,
-// held until the process ends (64 MiB: the largest workspace the split plan
-// asks for, about 768 partial sums of a 64 x 32 x 9 block, is 54 MiB).  In
+// held until the process ends (72 MiB: the largest workspace the split plan
+// asks for, about 768 partial sums of a 64 x 32 x 9 block, is 55 MiB).  In
 // host code `scratch` names a host-side stand-in, never the device memory:
 // kernels get the address hipGetSymbolAddress returns on each device.
-static constexpr int64_t kScratchFloats = int64_t(16) << 20;
+static constexpr int64_t kScratchFloats = int64_t(18) << 20;
 static __device__ __align__(256) float scratch[kScratchFloats];
 
 namespace {
@@ -1403,18 +1451,26 @@ void wgrad_run(int32_t n, int32_t cin, int32_t cout, int32_t h, int32_t w, const
     const WgradPlan pl = wgrad_plan(n, cin, cout, h, w);
     // partial rows [split][m weight sums | cout bias sums]
     float *bp = db ? work + m : nullptr;
+    const int ct = wgrad_ct(cout);
+    const int64_t blocks = (int64_t)((cout + ct - 1) / ct) * ((cin + 31) / 32);
     if (pl.c1) {
       hipLaunchKernelGGL(conv1_wgrad_kernel, dim3(pl.splits), dim3(BS), 0, s, n, cout, h, w, x, dz, work, stride,
                          pl.chunk, bp);
+    } else if (pl.tiled && (((uintptr_t)dz | (uintptr_t)x) & 15) == 0) {
+      auto *k = ct == 32 ? &conv_wgrad_mfma_kernel<32, false> : &conv_wgrad_mfma_kernel<64, false>;
+      hipLaunchKernelGGL(k, dim3(xcd_grid(blocks * pl.splits)), dim3(BS), 0, s, n, cin, cout, h, w, x, dz, work, stride,
+                         pl.chunk, (void *)bp, pl.splits);
     } else {
-      // (whole tiles at odd addresses are loaded element by element, like ragged ones)
-      const bool vec = pl.tiled && ((uintptr_t)dz & 15) == 0 && ((uintptr_t)x & 15) == 0;
-      const int ct = wgrad_ct(cout);
-      const dim3 g(xcd_grid((int64_t)((cout + ct - 1) / ct) * ((cin + 31) / 32) * pl.splits));
-      auto *k = ct == 32 ? (vec ? &conv_wgrad_mfma_kernel<32, false> : &conv_wgrad_mfma_kernel<32, true>)
-                         : (vec ? &conv_wgrad_mfma_kernel<64, false> : &conv_wgrad_mfma_kernel<64, true>);
-      hipLaunchKernelGGL(k, g, dim3(BS), 0, s, n, cin, cout, h, w, x, dz, work, stride, pl.chunk, bp,
-                         pl.splits);
+      // any shape, any address: partial rows [split][m weight sums], then (8-byte
+      // aligned) the bias sums [split][cout] in FP64
+      double *b64 = (double *)(((uintptr_t)(work + pl.splits * m) + 7) & ~(uintptr_t)7);
+      auto *k = ct == 32 ? &conv_wgrad_mfma_kernel<32, true> : &conv_wgrad_mfma_kernel<64, true>;
+      hipLaunchKernelGGL(k, dim3(xcd_grid(blocks * pl.splits)), dim3(BS), 0, s, n, cin, cout, h, w, x, dz, work, m,
+                         pl.chunk, db ? (void *)b64 : nullptr, pl.splits);
+      if (db) launch_split_sum2(work, pl.splits, m, dw, b64, cout, db, s);
+      else launch_split_sum(work, pl.splits, m, m, dw, s);
+      FDTD_HIP(hipGetLastError());
+      return;
     }
     if (db && db == dw + m) {  // contiguous weight and bias gradients: one reduction
       launch_split_sum(work, pl.splits, stride, m + cout, dw, s);
