@@ -661,11 +661,12 @@ __global__ void __launch_bounds__(BS) conv_wgrad_mfma_kernel(int nimg, int cin, 
   uint4 dv[DV], xa[XR], xb[XR];
   uint32_t xl[XR], xr[XR];
   bool okd[DV], okx[XR];  // RAG: the row exists; the loaded rows are cut when they are stored
-  int cx0 = 0;
+  int cx0 = 0, cy0 = 0;
   auto load_tile = [&](int T) {
     const int n = T / tiles_img, rem = T - n * tiles_img;
     const int y0 = (rem / tx_n) * GY, x0 = (rem % tx_n) * GX;
     cx0 = x0;
+    cy0 = y0;
 #pragma unroll
     for (int k = 0; k < DV; ++k) {
       const int v = t + k * BS;
@@ -750,19 +751,17 @@ __global__ void __launch_bounds__(BS) conv_wgrad_mfma_kernel(int nimg, int cin, 
       *(uint4 *)(d1 + 8) = uint4{W[4], W[5], W[6], W[7]};
       *(uint4 *)d2 = uint4{S2[0], S2[1], S2[2], S2[3]};
       *(uint4 *)(d2 + 8) = uint4{S2[4], S2[5], S2[6], S2[7]};
+      if (RAG) d0[w - cx0 < GX ? w - cx0 : (GY + 2 - r) * GX] = 0;  // (else behind the channel's rows)
     }
   };
-  if (T0 < T1) load_tile(T0);
-  for (int T = T0; T < T1; ++T) {
-    store_tile();
-    __syncthreads();
-    if (T + 1 < T1) load_tile(T + 1);
+  // taps of kernel rows k0 .. k1 - 1 over the tile
+  auto multiply = [&](auto k0, auto k1) {
 #pragma unroll
     for (int ks = 0; ks < GP / 32; ++ks) {
       const int py = 2 * ks + (kq >> 1), px = 8 * (kq & 1);
       const bf8 av = *(const bf8 *)(Ds + (16 * cw + l16) * DST + 32 * ks + 8 * kq);
 #pragma unroll
-      for (int tp = 0; tp < 9; ++tp) {
+      for (int tp = 3 * decltype(k0)::value; tp < 3 * decltype(k1)::value; ++tp) {
         const int ky = tp / 3, kx = tp - 3 * ky;
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) {
@@ -770,6 +769,32 @@ __global__ void __launch_bounds__(BS) conv_wgrad_mfma_kernel(int nimg, int cin, 
           acc[nt][tp] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bv, acc[nt][tp], 0, 0, 0);
         }
       }
+    }
+  };
+  using C0 = std::integral_constant<int, 0>;
+  using C1 = std::integral_constant<int, 1>;
+  using C3 = std::integral_constant<int, 3>;
+  if (T0 < T1) load_tile(T0);
+  for (int T = T0; T < T1; ++T) {
+    store_tile();
+    __syncthreads();
+    // A tile that hangs over the image: the gradients beyond it are zero, and where a
+    // tap pairs them with the image's last column (kx = 0) or last row (ky = 0) the
+    // input has to be zero too, since zero times an infinite input is not zero.  That
+    // column of the copy shifted by kx = 0 serves no other pair (zeroed when the row
+    // is stored); the row does, so the other taps go first.
+    const int py1 = h - cy0;  // rows inside the image
+    if (T + 1 < T1) load_tile(T + 1);
+    if constexpr (RAG) {
+      multiply(C1{}, C3{});
+      if (py1 < GY) {
+        __syncthreads();
+        if (t < 192) *(uint4 *)(Xs + (t >> 1) * XCI + py1 * GX + 8 * (t & 1)) = uint4{0u, 0u, 0u, 0u};
+        __syncthreads();
+      }
+      multiply(C0{}, C1{});
+    } else {
+      multiply(C0{}, C3{});
     }
     __syncthreads();
   }

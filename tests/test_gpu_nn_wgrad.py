@@ -4,6 +4,7 @@ import math
 
 import pytest
 import torch
+import torch.nn.functional as Fn
 
 import test_gpu_nn as T
 from test_gpu_nn import nn  # noqa: F401 (fixture)
@@ -47,3 +48,24 @@ def test_bias_gradient_is_rounded_once(nn, n, cin, cout, h, w, shift, joined):  
         want = math.fsum(v.tolist())
         ulp = 2.0 ** (math.floor(math.log2(max(abs(want), 1e-30))) - 23)
         assert abs(db[c].item() - want) <= 0.5 * ulp + 2.0 ** -40 * v.abs().sum().item(), (c, db[c].item(), want)
+
+
+@pytest.mark.parametrize("n,cin,cout,h,w", [(2, 20, 36, 13, 19), (1, 40, 33, 9, 17), (3, 5, 6, 5, 7), (2, 33, 20, 1, 40)])
+@pytest.mark.parametrize("where", ["corner", "right", "bottom"])
+def test_infinities_stay_in_their_own_sums(nn, n, cin, cout, h, w, where):  # noqa: F811
+    """An infinite input value at the last row or column of an image reaches the taps that
+    multiply it by a gradient of that image, and no others (a tile hangs over the
+    image there, and zero times infinity is not zero)."""
+    g = torch.Generator().manual_seed(h * w)
+    x = T.bf16_round(torch.randn(n, cin, h, w, generator=g))
+    dz = T.bf16_round(torch.randn(n, cout, h, w, generator=g))
+    y, c = {"corner": (h - 1, w - 1), "right": (h // 2, w - 1), "bottom": (h - 1, w // 2)}[where]
+    x[n - 1, cin - 1, y, c] = float("inf")
+    dw, db = wgrad(nn, x, dz, n, cin, cout, h, w)
+    cols = Fn.unfold(x.double(), 3, padding=1)  # [n][cin 9][h w]
+    want = sum(dz[k].double().reshape(cout, -1) @ cols[k].T for k in range(n)).view(cout, cin, 3, 3)
+    assert torch.equal(torch.isfinite(dw), torch.isfinite(want))
+    ok = torch.isfinite(want)
+    sw = (dz.abs().sum() * x[torch.isfinite(x)].abs().max()).item()
+    assert (dw.double() - want)[ok].abs().max().item() <= 2e-6 * sw
+    assert torch.isfinite(db).all()
