@@ -593,6 +593,78 @@ void launch_conv(int n, int cin, int cout, int h, int w, const uint16_t *x, cons
   hipLaunchKernelGGL(conv_fwd_kernel, g, dim3(BS), 0, s, cin, cout, h, w, x, wt, bias, z, a, mask);
 }
 
+// Partial weight gradients over one range of pixels q = (n, p) of the batch:
+// part[split][co][k] = sum_q dz[co][q] xhat[k][q], and with bpart the bias sums
+// bpart[split][co] = sum_q dz[co][q].  For images that would fill less than a
+// quarter of the 8 x 16-pixel tiles of the kernel below: here the pixels of all
+// images follow one another, at an index division per element.  us with / without
+// (64 -> 64 channels): 4096 images of 1 x 1 34 / 1187, 1024 of 4 x 4 59 / 93, 512 of
+// 5 x 5 51 / 69, 8 of 4000 x 1 76 / 242; the other way 512 of 6 x 6 62 / 57, of
+// 7 x 7 73 / 54.  grid (ceil(K/64), ceil(cout/64), splits).
+__global__ void __launch_bounds__(BS) conv_wgrad_kernel(int nimg, int cin, int cout, int h, int w,
+                                                       const uint16_t *__restrict__ x, const uint16_t *__restrict__ dz,
+                                                       float *__restrict__ part, int chunk,
+                                                       double *__restrict__ bpart) {
+  __shared__ uint16_t As[TM][TK + PAD];  // dz: co x q
+  __shared__ uint16_t Bs[TK][TN + PAD];  // xhat: q x k
+  const int HW = h * w, K = cin * 9;
+  const int64_t P = (int64_t)nimg * HW;
+  const int k0 = blockIdx.x * TN, co0 = blockIdx.y * TM, split = blockIdx.z;
+  const int64_t qb = (int64_t)split * chunk, qe = min(P, qb + chunk);
+  const int t = threadIdx.x, wave = t >> 6, lane = t & 63;
+  f4 acc[4];
+#pragma unroll
+  for (int s = 0; s < 4; ++s) acc[s] = f4{0.f, 0.f, 0.f, 0.f};
+  const bool with_bias = bpart != nullptr && k0 == 0;
+  double bsum = 0;
+  for (int64_t q0 = qb; q0 < qe; q0 += TK) {
+    {
+      const int r = t >> 2, c = (t & 3) * 4, co = co0 + r;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int64_t q = q0 + c + j;
+        As[r][c + j] = (co < cout && q < qe) ? dz[(size_t)co * P + q] : (uint16_t)0;
+        if (with_bias) bsum += bf2f(As[r][c + j]);
+      }
+    }
+    {
+      const int qq = t >> 4, c = (t & 15) * 4;
+      const int64_t q = q0 + qq;
+      const bool qok = q < qe;
+      const int64_t n = qok ? q / HW : 0;
+      const int p = qok ? (int)(q - n * HW) : 0;
+      const int y = p / w, xx = p - y * w;
+      const uint16_t *xn = x + (size_t)n * HW;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int k = k0 + c + j;
+        uint16_t v = 0;
+        if (qok && k < K) {
+          const int tap = k / cin, ci = k - tap * cin, ky = tap / 3, kx = tap - ky * 3;
+          const int iy = y + ky - 1, ix = xx + kx - 1;
+          if (iy >= 0 && iy < h && ix >= 0 && ix < w) v = xn[(size_t)ci * P + iy * w + ix];
+        }
+        Bs[qq][c + j] = v;
+      }
+    }
+    __syncthreads();
+    mfma_step(As, Bs, wave, lane, acc);
+    __syncthreads();
+  }
+#pragma unroll
+  for (int s = 0; s < 4; ++s)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int co = co0 + 16 * wave + 4 * (lane >> 4) + j, k = k0 + 16 * s + (lane & 15);
+      if (co < cout && k < K) part[((size_t)split * cout + co) * K + k] = acc[s][j];
+    }
+  if (with_bias) {
+    bsum += __shfl_xor(bsum, 1, 64);
+    bsum += __shfl_xor(bsum, 2, 64);
+    if ((t & 3) == 0 && co0 + (t >> 2) < cout) bpart[(size_t)split * cout + co0 + (t >> 2)] = bsum;
+  }
+}
+
 // Weight gradient, LDS-tiled for cin % 32 == 0, h % 8 == 0, w % 16 == 0 and
 // 16-byte aligned x and dz:
 // part[split][co][tap][ci] = sum over the split's pixel tiles of
@@ -915,8 +987,8 @@ __global__ void __launch_bounds__(BS) conv1_wgrad_kernel(int nimg, int cout, int
 // Split plan of the weight gradient: which kernel, how many partial sums, pixel
 // tiles per split.
 struct WgradPlan {
-  bool tiled, c1;  // 16-byte loads of whole tiles; one-input-channel kernel
-  int splits, chunk;
+  bool tiled, c1, packed;  // 16-byte loads of whole tiles; one-input-channel kernel; pixels packed
+  int splits, chunk;       // (chunk: tiles, packed: pixels)
 };
 
 // Output-channel tile of the tiled weight gradient.
@@ -956,10 +1028,16 @@ WgradPlan wgrad_plan(int n, int cin, int cout, int h, int w) {
     pl.splits = (tiles + per - 1) / per;
     return pl;
   }
+  const int64_t tiles = (int64_t)n * ((h + GY - 1) / GY) * ((w + GX - 1) / GX), P = (int64_t)n * h * w;
+  if (4 * P < tiles * GP) {
+    pl.packed = true;
+    pl.splits = wgrad_splits(n, cin, cout, h, w);
+    pl.chunk = (int)((P + pl.splits - 1) / pl.splits + TK - 1) / TK * TK;
+    return pl;
+  }
   // ragged shapes: as many workgroups, at most the splits of wgrad_splits
   const int ct = wgrad_ct(cout);
   const int64_t groups = (int64_t)((cout + ct - 1) / ct) * ((cin + 31) / 32);
-  const int64_t tiles = (int64_t)n * ((h + GY - 1) / GY) * ((w + GX - 1) / GX);
   const int64_t want = std::max<int64_t>(1, std::min<int64_t>((768 + groups - 1) / groups, wgrad_splits(n, cin, cout, h, w)));
   pl.chunk = (int)((tiles + want - 1) / want);
   pl.splits = (int)((tiles + pl.chunk - 1) / pl.chunk);
@@ -1489,9 +1567,15 @@ void wgrad_run(int32_t n, int32_t cin, int32_t cout, int32_t h, int32_t w, const
       // any shape, any address: partial rows [split][m weight sums], then (8-byte
       // aligned) the bias sums [split][cout] in FP64
       double *b64 = (double *)(((uintptr_t)(work + pl.splits * m) + 7) & ~(uintptr_t)7);
-      auto *k = ct == 32 ? &conv_wgrad_mfma_kernel<32, true> : &conv_wgrad_mfma_kernel<64, true>;
-      hipLaunchKernelGGL(k, dim3(xcd_grid(blocks * pl.splits)), dim3(BS), 0, s, n, cin, cout, h, w, x, dz, work, m,
-                         pl.chunk, db ? (void *)b64 : nullptr, pl.splits);
+      if (pl.packed) {
+        const dim3 g((cin * 9 + TN - 1) / TN, (cout + TM - 1) / TM, pl.splits);
+        hipLaunchKernelGGL(conv_wgrad_kernel, g, dim3(BS), 0, s, n, cin, cout, h, w, x, dz, work, pl.chunk,
+                           db ? b64 : nullptr);
+      } else {
+        auto *k = ct == 32 ? &conv_wgrad_mfma_kernel<32, true> : &conv_wgrad_mfma_kernel<64, true>;
+        hipLaunchKernelGGL(k, dim3(xcd_grid(blocks * pl.splits)), dim3(BS), 0, s, n, cin, cout, h, w, x, dz, work, m,
+                           pl.chunk, db ? (void *)b64 : nullptr, pl.splits);
+      }
       if (db) launch_split_sum2(work, pl.splits, m, dw, b64, cout, db, s);
       else launch_split_sum(work, pl.splits, m, m, dw, s);
       FDTD_HIP(hipGetLastError());

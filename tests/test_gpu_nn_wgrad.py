@@ -69,3 +69,21 @@ def test_infinities_stay_in_their_own_sums(nn, n, cin, cout, h, w, where):  # no
     sw = (dz.abs().sum() * x[torch.isfinite(x)].abs().max()).item()
     assert (dw.double() - want)[ok].abs().max().item() <= 2e-6 * sw
     assert torch.isfinite(db).all()
+
+
+# at the edge of a quarter of the 8 x 16 tiles (packed pixels below): one pixel, rows,
+# columns, 4 x 8 (a quarter) and one pixel less, several tiles, channels around 64
+@pytest.mark.parametrize("n,cin,cout,h,w", [(1, 1, 1, 1, 1), (5, 3, 2, 1, 1), (3, 65, 63, 1, 31), (2, 17, 65, 31, 1),
+                                             (4, 33, 20, 4, 8), (4, 33, 20, 1, 32), (700, 20, 64, 2, 3), (2, 64, 64, 9, 17),
+                                             (40, 16, 130, 5, 5)])
+def test_images_that_fill_little_of_a_tile(nn, n, cin, cout, h, w):  # noqa: F811
+    """Both sides of the rule that packs the pixels of small images, with the
+    tolerance of the other weight gradients."""
+    g = torch.Generator().manual_seed(n + h)
+    x = T.bf16_round(torch.randn(n, cin, h, w, generator=g))
+    dz = T.bf16_round(torch.randn(n, cout, h, w, generator=g))
+    dw, db = wgrad(nn, x, dz, n, cin, cout, h, w)
+    cols = Fn.unfold(x.double(), 3, padding=1)
+    want = sum(dz[k].double().reshape(cout, -1) @ cols[k].T for k in range(n)).view(cout, cin, 3, 3)
+    assert (dw.double() - want).abs().max().item() <= 2e-6 * (dz.abs().sum() * x.abs().max()).item()
+    assert torch.allclose(db.double(), dz.double().sum(dim=(0, 2, 3)), rtol=1e-6, atol=1e-5)
