@@ -225,7 +225,7 @@ __global__ void __launch_bounds__(BS) conv_fwd_kernel(int cin, int cout, int h, 
 }
 
 // The same convolution, LDS-tiled for cin % 32 == 0, h, w multiples of 16 and
-// 16-byte aligned x and weights, on v_mfma_f32_16x16x32_bf16.  A workgroup owns
+// 16-byte aligned weights (ODD: x at any address, the same bits), on v_mfma_f32_16x16x32_bf16.  A workgroup owns
 // 32 output channels x 16 x 16 pixels of one image; per chunk of 32 input
 // channels it stages the 18 x 18 halo tile channel-last in LDS (eight channels of
 // one pixel are one 16-byte LDS read) and the weights of all nine taps, then each
@@ -246,7 +246,19 @@ constexpr int XST = 40;                 // LDS stride between staged pixels (80 
 constexpr int WST = 40;                 // LDS stride between staged (tap, co) weight rows
 constexpr int TT = 16, HT = TT + 2;     // output tile side, halo tile side
 
-template <bool ONE>
+// Elements sh (0 .. 7) onwards of u, two a word.
+template <int N>
+__device__ __forceinline__ void shift_down(uint32_t (&u)[N], int sh) {
+  const uint32_t two = sh & 4 ? ~0u : 0u, one = sh & 2 ? ~0u : 0u;
+#pragma unroll
+  for (int k = 0; k + 2 < N; ++k) u[k] ^= (u[k] ^ u[k + 2]) & two;
+#pragma unroll
+  for (int k = 0; k + 1 < N; ++k) u[k] ^= (u[k] ^ u[k + 1]) & one;
+#pragma unroll
+  for (int k = 0; k + 1 < N; ++k) u[k] = __builtin_amdgcn_alignbit(u[k + 1], u[k], 16 * (sh & 1));
+}
+
+template <bool ONE, bool ODD>
 __global__ void __launch_bounds__(BS) conv_fwd_mfma_kernel(int cin, int cout, int h, int w,
                                                                const uint16_t *__restrict__ x,
                                                                const uint16_t *__restrict__ wt,
@@ -264,7 +276,12 @@ __global__ void __launch_bounds__(BS) conv_fwd_mfma_kernel(int cin, int cout, in
   const int co0 = item % cot * 16 * MT;
   const int t = threadIdx.x, wave = t >> 6, lane = t & 63, l16 = lane & 15, kq = lane >> 4;
   const size_t cs = (size_t)nimg * HW;
-  uint4 xv[4], xt = {0u, 0u, 0u, 0u}, wr[NWV];
+  // x off a 16-byte address by sh elements, the same for every row (w is a multiple of
+  // 16): aligned vectors, each with an element of the row in it, shifted when they
+  // are used
+  constexpr int NV = ODD ? 3 : 2;
+  const int sh = ODD ? __builtin_amdgcn_readfirstlane((int)((uintptr_t)x >> 1) & 7) : 0;
+  uint4 xv[2 * NV], xt[2] = {}, wr[NWV];
   uint32_t xe[4], te2 = 0;  // halo columns
   // rows 0 .. 15: channels c, c + 1 of row r; rows 16, 17: 8 pixels of channel tc
   const int c = 2 * (t & 15), r = t >> 4, tc = (t >> 1) & 31, tr = 16 + (t >> 6), th = t & 1;
@@ -276,24 +293,34 @@ __global__ void __launch_bounds__(BS) conv_fwd_mfma_kernel(int cin, int cout, in
     const int xl = max(lx0 - 1, 0), xr = min(lx0 + TT, w - 1);
     const uint16_t *r0 = x + (size_t)(c0 + c) * cs + (size_t)n * HW + (size_t)max(ly0 - 1 + r, 0) * w;
     const uint16_t *r1 = r0 + cs;
-    xv[0] = *(const uint4 *)(r0 + lx0);
-    xv[1] = *(const uint4 *)(r0 + lx0 + 8);
-    xv[2] = *(const uint4 *)(r1 + lx0);
-    xv[3] = *(const uint4 *)(r1 + lx0 + 8);
+#pragma unroll
+    for (int k = 0; k < NV; ++k) {
+      xv[k] = *(const uint4 *)(r0 - sh + lx0 + 8 * k);
+      xv[NV + k] = *(const uint4 *)(r1 - sh + lx0 + 8 * k);
+    }
     xe[0] = r0[xl];
     xe[1] = r1[xl];
     xe[2] = r0[xr];
     xe[3] = r1[xr];
     if (t < 128) {
       const uint16_t *rt = x + (size_t)(c0 + tc) * cs + (size_t)n * HW + (size_t)min(ly0 - 1 + tr, h - 1) * w;
-      xt = *(const uint4 *)(rt + lx0 + 8 * th);
+      xt[0] = *(const uint4 *)(rt - sh + lx0 + 8 * th);
+      if (ODD) xt[1] = *(const uint4 *)(rt - sh + lx0 + 8 * th + 8);
       te2 = rt[th ? xr : xl];
     }
   };
   auto store_x = [&]() {
     const bool ok = ly0 - 1 + r >= 0, left = lx0 > 0, right = lx0 + TT < w;
-    const uint32_t u0[8] = {xv[0].x, xv[0].y, xv[0].z, xv[0].w, xv[1].x, xv[1].y, xv[1].z, xv[1].w};
-    const uint32_t u1[8] = {xv[2].x, xv[2].y, xv[2].z, xv[2].w, xv[3].x, xv[3].y, xv[3].z, xv[3].w};
+    uint32_t u0[4 * NV], u1[4 * NV];
+#pragma unroll
+    for (int k = 0; k < NV; ++k) {
+      u0[4 * k] = xv[k].x; u0[4 * k + 1] = xv[k].y; u0[4 * k + 2] = xv[k].z; u0[4 * k + 3] = xv[k].w;
+      u1[4 * k] = xv[NV + k].x; u1[4 * k + 1] = xv[NV + k].y; u1[4 * k + 2] = xv[NV + k].z; u1[4 * k + 3] = xv[NV + k].w;
+    }
+    if constexpr (ODD) {
+      shift_down(u0, sh);
+      shift_down(u1, sh);
+    }
     uint16_t *d = Xs + r * HT * XST + c;
     *(uint32_t *)d = ok && left ? xe[0] | (xe[1] << 16) : 0u;
 #pragma unroll
@@ -305,7 +332,8 @@ __global__ void __launch_bounds__(BS) conv_fwd_mfma_kernel(int cin, int cout, in
     if (t < 128) {
       const bool okt = ly0 - 1 + tr < h;
       uint16_t *p = Xs + (tr * HT + 8 * th + 1) * XST + tc;
-      const uint32_t v[4] = {xt.x, xt.y, xt.z, xt.w};
+      uint32_t v[8] = {xt[0].x, xt[0].y, xt[0].z, xt[0].w, xt[1].x, xt[1].y, xt[1].z, xt[1].w};
+      if constexpr (ODD) shift_down(v, sh);
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         p[2 * q * XST] = okt ? (uint16_t)v[q] : (uint16_t)0;
@@ -562,7 +590,7 @@ __global__ void __launch_bounds__(BS) conv1_fwd_kernel(int cout, int h, int w, c
 }
 
 // One forward convolution launch: the LDS-tiled kernel where the shape and
-// the alignment allow it, else the one for any shape, or, beyond
+// the weights' alignment allow it, else the one for any shape, or, beyond
 // 384 input channels, the one that stages a step at a time.
 void launch_conv(int n, int cin, int cout, int h, int w, const uint16_t *x, const uint16_t *wt, const float *bias,
                  float *z, uint16_t *a, const uint16_t *mask, hipStream_t s) {
@@ -571,10 +599,12 @@ void launch_conv(int n, int cin, int cout, int h, int w, const uint16_t *x, cons
                        z, a, mask);
     return;
   }
-  if (cin % CC == 0 && h % TT == 0 && w % TT == 0 && (((uintptr_t)wt | (uintptr_t)x) & 15) == 0) {
+  if (cin % CC == 0 && h % TT == 0 && w % TT == 0 && ((uintptr_t)wt & 15) == 0) {
     const int tiles = (h / TT) * (w / TT);
     const dim3 g(xcd_grid((int64_t)tiles * ((cout + 16 * MT - 1) / (16 * MT)) * n));
-    auto *k = cin == CC ? &conv_fwd_mfma_kernel<true> : &conv_fwd_mfma_kernel<false>;
+    const bool odd = (uintptr_t)x & 15;
+    auto *k = cin == CC ? (odd ? &conv_fwd_mfma_kernel<true, true> : &conv_fwd_mfma_kernel<true, false>)
+                        : (odd ? &conv_fwd_mfma_kernel<false, true> : &conv_fwd_mfma_kernel<false, false>);
     hipLaunchKernelGGL(k, g, dim3(BS), 0, s, cin, cout, h, w, x, wt, bias, z, a, mask, n);
     return;
   }

@@ -1,0 +1,40 @@
+"""Convolutions whose inputs lie where the kernels' wide loads would not expect them."""
+import math
+
+import pytest
+import torch
+
+import test_gpu_nn as T
+from test_gpu_nn import nn  # noqa: F401 (fixture)
+
+pytestmark = pytest.mark.gpu
+
+
+def shifted(t, by):
+    b = torch.full((t.numel() + 8,), 0x7fc0, dtype=t.dtype, device="cuda")
+    b[by:by + t.numel()] = t.reshape(-1)
+    return b[by:by + t.numel()]
+
+
+@pytest.mark.parametrize("n,cin,cout,h,w", [(2, 32, 64, 16, 16), (1, 32, 33, 48, 32), (3, 64, 70, 32, 16),
+                                             (1, 416, 20, 16, 32)])
+@pytest.mark.parametrize("by", [1, 4])
+def test_regular_shape_with_x_off_a_16_byte_address(nn, n, cin, cout, h, w, by):  # noqa: F811
+    """Forward and data gradient of a regular shape do not depend on where x lies: the
+    same bits as at an aligned address (one chunk of channels, several, beyond 384)."""
+    g = torch.Generator().manual_seed(cin)
+    x = T.bits(T.bf16_round(torch.randn(cin, n, h, w, generator=g)))
+    wt = T.bits(T.bf16_round(torch.randn(cout, 9 * cin, generator=g) / math.sqrt(9 * cin)))
+    bias = torch.randn(cout, generator=g).cuda()
+    act = T.bits(torch.relu(torch.randn(cout, n, h, w, generator=g)))
+    out = []
+    for xs in (x.reshape(-1), shifted(x, by)):
+        z = torch.empty(cout * n * h * w, device="cuda")
+        a = torch.empty(cout * n * h * w, dtype=torch.int16, device="cuda")
+        dza = torch.empty_like(a)
+        nn.conv3x3(xs, wt, bias, n, cin, cout, h, w, z=z, a=a)
+        # the data gradient of a layer from cout to cin channels: x is its dz
+        nn.conv3x3_dgrad_relu(xs, None, wt, act, dza, n, cout, cin, h, w)
+        torch.cuda.synchronize()
+        out.append((z.cpu(), a.cpu(), dza.cpu()))
+    assert all(torch.equal(p, q) for p, q in zip(*out))
