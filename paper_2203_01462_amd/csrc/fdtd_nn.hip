@@ -407,8 +407,9 @@ __global__ void __launch_bounds__(BS) conv_fwd_mfma_kernel(int cin, int cout, in
 // and beyond cin), and its wavefronts walk k = (tap, channel) in steps of 16 as
 // conv_fwd_kernel does - the same matrix instructions in the same order, so for
 // cin % 16 == 0 the same bits - with the weights' fragments read ahead from
-// global memory.  That kernel's time is its staging: an index division and a
-// 2-byte load per element and tap.  4 x 48 x 50 x 75 -> 80 channels:
+// global memory.  That kernel's time is its staging (an index division and a
+// 2-byte load per element and tap), which it is still the better one for where this
+// one would pad much (conv_packs).  4 x 48 x 50 x 75 -> 80 channels:
 // 62 us -> 15.5.
 constexpr int GT = 8, GH = GT + 2, AHEAD = 9;  // 9 divides the steps
 
@@ -589,9 +590,28 @@ __global__ void __launch_bounds__(BS) conv1_fwd_kernel(int cout, int h, int w, c
   }
 }
 
+// Which of the two kernels for any shape?  conv_fwd_kernel packs the pixels of an
+// image and the taps' channels: ceil(9 cin / 16) steps on ceil(hw / 64) blocks, each
+// step staged element by element.  conv_gen_kernel pads both: nine times
+// ceil(cin / 16) much cheaper steps, after a halo, on whole 8 x 8 tiles; channel
+// counts that are no multiple of 4 load its weights element by element.  The costs
+// below, in steps of the former, were fitted to 2011 measured layers (1 to 384
+// channels, 1 to 192 out, images from one pixel over rows and columns to 333 x 517):
+// the slower kernel is taken by more than 10% in 24 of them.  us, conv_fwd_kernel
+// against conv_gen_kernel: 32 x (3 -> 16) x 127^2 35 / 55, 32 x (1 -> 128) x 50^2
+// 16 / 33, 8 x (48 -> 80) x 4000 x 1 48 / 69; 4 x (48 -> 80) x 16^2 38 / 8.
+bool conv_packs(int n, int cin, int cout, int h, int w) {
+  if (cin > 384) return true;  // (its halo does not fit the LDS)
+  const double images = (double)n * ((cout + TM - 1) / TM);
+  const double packed = images * (((int64_t)h * w + TN - 1) / TN);
+  const double tiled = images * ((h + GT - 1) / GT) * ((w + GT - 1) / GT);
+  const int steps = (9 * cin + 15) / 16, padded = 9 * ((cin + 15) / 16);
+  const double step = cin % 4 == 0 ? 0.115 : cout > 32 ? 0.4 : 0.21;
+  return std::max(1.0, packed / 896) * (steps + 0.4) < std::max(1.0, tiled / 512) * (0.6 + step * padded);
+}
+
 // One forward convolution launch: the LDS-tiled kernel where the shape and
-// the weights' alignment allow it, else the one for any shape, or, beyond
-// 384 input channels, the one that stages a step at a time.
+// the weights' alignment allow it, else one of the two for any shape.
 void launch_conv(int n, int cin, int cout, int h, int w, const uint16_t *x, const uint16_t *wt, const float *bias,
                  float *z, uint16_t *a, const uint16_t *mask, hipStream_t s) {
   if (cin == 1 && cout <= 64) {
@@ -608,7 +628,7 @@ void launch_conv(int n, int cin, int cout, int h, int w, const uint16_t *x, cons
     hipLaunchKernelGGL(k, g, dim3(BS), 0, s, cin, cout, h, w, x, wt, bias, z, a, mask, n);
     return;
   }
-  if (cin <= 384) {  // the halo of all channels fits the LDS
+  if (!conv_packs(n, cin, cout, h, w)) {
     const dim3 g(xcd_grid((int64_t)((h + GT - 1) / GT) * ((w + GT - 1) / GT) * ((cout + TM - 1) / TM) * n));
     auto pick = [&](auto vec) {
       constexpr bool V = decltype(vec)::value;

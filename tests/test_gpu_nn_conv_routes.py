@@ -38,3 +38,13 @@ def test_regular_shape_with_x_off_a_16_byte_address(nn, n, cin, cout, h, w, by):
         torch.cuda.synchronize()
         out.append((z.cpu(), a.cpu(), dza.cpu()))
     assert all(torch.equal(p, q) for p, q in zip(*out))
+
+
+# few channels, single rows and columns, tiny images: either side of the rule between
+# the two kernels for any shape
+@pytest.mark.parametrize("n,cin,cout,h,w", [(8, 3, 16, 64, 65), (8, 1, 128, 30, 31), (4, 2, 70, 33, 65), (2, 17, 65, 1, 200),
+                                             (2, 40, 33, 200, 1), (64, 8, 8, 2, 100), (3, 12, 96, 40, 41), (300, 6, 10, 1, 1),
+                                             (64, 100, 20, 3, 50), (1, 384, 70, 1, 33)])
+def test_both_kernels_for_any_shape(nn, n, cin, cout, h, w):  # noqa: F811
+    T.test_conv_forward(nn, n, cin, cout, h, w)
+    T.test_conv_backward(nn, n, cin, cout, h, w)
