@@ -34,8 +34,12 @@
  * the batch (weight and bias gradients, the head, the loss) are taken in a
  * fixed order, so results do not depend on scheduling.
  *
- * Device memory: no function allocates any; fdtd_nn_conv3x3_wgrad_noalloc uses
- * an array that is part of the library.
+ * Device memory: no function keeps any; fdtd_nn_conv3x3_wgrad_noalloc uses
+ * an array that is part of the library.  A convolution must not write over its
+ * input, unless (without a fused ReLU mask) the input has a multiple of 32 channels,
+ * the image sides are multiples of 16 and the weights lie on a 16-byte address: it
+ * then copies the input first, into memory taken from the device's stream-ordered
+ * pool and given back in stream order.
  */
 #ifndef FDTD_NN_H
 #define FDTD_NN_H

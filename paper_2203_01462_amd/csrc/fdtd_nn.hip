@@ -610,6 +610,27 @@ bool conv_packs(int n, int cin, int cout, int h, int w) {
   return std::max(1.0, packed / 896) * (steps + 0.4) < std::max(1.0, tiled / 512) * (0.6 + step * padded);
 }
 
+// A copy of device memory that lives until the stream has used it.
+struct StreamCopy {
+  void *p = nullptr;
+  hipStream_t s;
+  StreamCopy(const void *src, size_t bytes, hipStream_t stream) : s(stream) {
+    FDTD_HIP(hipMallocAsync(&p, bytes, s));
+    const hipError_t e = hipMemcpyAsync(p, src, bytes, hipMemcpyDeviceToDevice, s);
+    if (e != hipSuccess) {
+      (void)hipFreeAsync(p, s);
+      FDTD_HIP(e);
+    }
+  }
+  StreamCopy(const StreamCopy &) = delete;
+  StreamCopy &operator=(const StreamCopy &) = delete;
+  ~StreamCopy() { (void)hipFreeAsync(p, s); }
+};
+
+bool overlap(const void *a, size_t na, const void *b, size_t nb) {
+  return a && b && (uintptr_t)a < (uintptr_t)b + nb && (uintptr_t)b < (uintptr_t)a + na;
+}
+
 // One forward convolution launch: the LDS-tiled kernel where the shape and
 // the weights' alignment allow it, else one of the two for any shape.
 void launch_conv(int n, int cin, int cout, int h, int w, const uint16_t *x, const uint16_t *wt, const float *bias,
@@ -623,6 +644,14 @@ void launch_conv(int n, int cin, int cout, int h, int w, const uint16_t *x, cons
     const int tiles = (h / TT) * (w / TT);
     const dim3 g(xcd_grid((int64_t)tiles * ((cout + 16 * MT - 1) / (16 * MT)) * n));
     const bool odd = (uintptr_t)x & 15;
+    const size_t nx = (size_t)cin * n * h * w, ny = (size_t)cout * n * h * w;
+    // in place: neighbouring tiles still read what this one writes
+    if (overlap(x, nx * sizeof(uint16_t), z, ny * sizeof(float)) ||
+        overlap(x, nx * sizeof(uint16_t), a, ny * sizeof(uint16_t))) {
+      const StreamCopy c(x, nx * sizeof(uint16_t), s);
+      launch_conv(n, cin, cout, h, w, (const uint16_t *)c.p, wt, bias, z, a, mask, s);
+      return;
+    }
     auto *k = cin == CC ? (odd ? &conv_fwd_mfma_kernel<true, true> : &conv_fwd_mfma_kernel<true, false>)
                         : (odd ? &conv_fwd_mfma_kernel<false, true> : &conv_fwd_mfma_kernel<false, false>);
     hipLaunchKernelGGL(k, g, dim3(BS), 0, s, cin, cout, h, w, x, wt, bias, z, a, mask, n);

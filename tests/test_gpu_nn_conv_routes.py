@@ -48,3 +48,31 @@ def test_regular_shape_with_x_off_a_16_byte_address(nn, n, cin, cout, h, w, by):
 def test_both_kernels_for_any_shape(nn, n, cin, cout, h, w):  # noqa: F811
     T.test_conv_forward(nn, n, cin, cout, h, w)
     T.test_conv_backward(nn, n, cin, cout, h, w)
+
+
+@pytest.mark.parametrize("n,cin,cout,h,w", [(2, 32, 32, 32, 48), (3, 64, 64, 16, 16), (1, 64, 32, 48, 32)])
+def test_convolution_in_place(nn, n, cin, cout, h, w):  # noqa: F811
+    """A regular convolution may write over its input: the activation over x, the FP32
+    output over a buffer that x is a part of; the same bits as into other memory."""
+    g = torch.Generator().manual_seed(h)
+    x = T.bits(T.bf16_round(torch.randn(cin, n, h, w, generator=g))).reshape(-1)
+    wt = T.bits(T.bf16_round(torch.randn(cout, 9 * cin, generator=g) / math.sqrt(9 * cin)))
+    px = n * h * w
+    z, a = torch.empty(cout * px, device="cuda"), torch.empty(cout * px, dtype=torch.int16, device="cuda")
+    nn.conv3x3(x, wt, None, n, cin, cout, h, w, z=z, a=a)
+    over = x.clone()
+    nn.conv3x3(over, wt, None, n, cin, cout, h, w, a=over)
+    buf = torch.empty(max(cout, cin) * px, device="cuda")  # FP32: twice the bytes of x
+    part = buf.view(torch.int16)[cin * px // 2:][:cin * px]
+    part.copy_(x)
+    nn.conv3x3(part, wt, None, n, cin, cout, h, w, z=buf)
+    torch.cuda.synchronize()
+    assert torch.equal(over[:cout * px].cpu(), a.cpu())
+    assert torch.equal(buf[:cout * px].cpu(), z.cpu())
+    # the data gradient of a layer from cout to cin channels over its dz
+    dz = torch.empty(max(cout, cin) * px, device="cuda")
+    part = dz.view(torch.int16)[:cin * px]
+    part.copy_(x)
+    nn.conv3x3_dgrad(part, None, wt, dz, n, cout, cin, h, w)
+    torch.cuda.synchronize()
+    assert torch.equal(dz[:cout * px].cpu(), z.cpu())
