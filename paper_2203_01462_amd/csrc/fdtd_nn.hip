@@ -1477,30 +1477,45 @@ __global__ void __launch_bounds__(BS) gap_linear_back_a_kernel(int nimg, int c, 
   da[i] = dout[n] * wl[ch] / (float)hw;
 }
 
-// out[n] = bl + sum_c wl[c] mean_p a[c][n][p]: one 1024-thread workgroup per
-// image, wavefront wv takes channels wv, wv + 16, ..., its lanes pixels
-// lane + 64 k (FP64 sums, a fixed order).  256 channels of 13 x 13 pixels: 22 us
-// (66 with 256 threads that divide an index per element).
-__global__ void __launch_bounds__(1024) gap_linear_kernel(int nimg, int c, int hw, const uint16_t *__restrict__ a,
+// out[n] = bl + sum_c wl[c] mean_p a[c][n][p]: a workgroup per image (or several, one
+// after another), FP64 sums in a fixed order.  From 64 pixels on (SMALL false) a
+// wavefront takes a channel, then the next one, its lanes the pixels lane + 64 k;
+// below, L lanes a channel and 64 / L channels side by side.  256 channels of 13 x 13
+// pixels, 32 images: 10 us (40 with 256 threads that divide an index per element);
+// 64 channels of one pixel, 4096 images: 8 (21 with 64 lanes per channel).
+template <bool SMALL>
+__global__ void __launch_bounds__(1024) gap_linear_kernel(int nimg, int c, int hw, int L, const uint16_t *__restrict__ a,
                                                            const float *__restrict__ wl, const float *__restrict__ bl,
                                                            float *__restrict__ out) {
   __shared__ double lds[16];
-  const int n = blockIdx.x, wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  double v = 0;
-  for (int ch = wv; ch < c; ch += 16) {
-    const uint16_t *row = a + ((size_t)ch * nimg + n) * hw;
-    double sp = 0;
+  const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63, waves = blockDim.x >> 6;
+  for (int n = blockIdx.x; n < nimg; n += gridDim.x) {
+    double v = 0;
+    if constexpr (SMALL) {
+      const int side = 64 / L, p = lane & (L - 1);
+      if (p < hw) {
 #pragma unroll 4
-    for (int p = lane; p < hw; p += 64) sp += bf2f(row[p]);
-    v += (double)wl[ch] * sp;
-  }
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, 64);
-  if (lane == 0) lds[wv] = v;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    double s = 0;
-    for (int k = 0; k < 16; ++k) s += lds[k];
-    out[n] = (float)(s / hw + bl[0]);
+        for (int ch = wv * side + lane / L; ch < c; ch += waves * side)
+          v += (double)wl[ch] * (double)bf2f(a[((size_t)ch * nimg + n) * hw + p]);
+      }
+    } else {
+      for (int ch = wv; ch < c; ch += 16) {
+        const uint16_t *row = a + ((size_t)ch * nimg + n) * hw;
+        double sp = 0;
+#pragma unroll 4
+        for (int p = lane; p < hw; p += 64) sp += bf2f(row[p]);
+        v += (double)wl[ch] * sp;
+      }
+    }
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, 64);
+    if (lane == 0) lds[wv] = v;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      double s = 0;
+      for (int k = 0; k < (SMALL ? waves : 16); ++k) s += lds[k];
+      out[n] = (float)(s / hw + bl[0]);
+    }
+    if (n + (int)gridDim.x < nimg) __syncthreads();
   }
 }
 
@@ -1854,7 +1869,19 @@ fdtd_status fdtd_nn_gap_linear(int32_t n, int32_t c, int32_t hw, const uint16_t 
                                float *out, void *stream) {
   return nguard([&] {
     need(n > 0 && c > 0 && hw > 0 && a && wl && bl && out);
-    hipLaunchKernelGGL(gap_linear_kernel, dim3(n), dim3(1024), 0, (hipStream_t)stream, n, c, hw, a, wl, bl, out);
+    int L = 1;
+    while (L < 64 && L < hw) L *= 2;
+    const dim3 grid(std::min(n, 1 << 21));
+    if (hw >= 64) {
+      hipLaunchKernelGGL(gap_linear_kernel<false>, grid, dim3(1024), 0, (hipStream_t)stream, n, c, hw, L, a, wl, bl, out);
+    } else {
+      // while two workgroups a CU hold the images, the more wavefronts the better; beyond,
+      // their number costs (4096 images of 64 channels, 9 pixels: 22 us with 1024
+      // threads)
+      const int threads = (int)std::min<int64_t>(n <= 512 ? 1024 : 256, ((int64_t)c * L + 63) / 64 * 64);
+      hipLaunchKernelGGL(gap_linear_kernel<true>, grid, dim3(threads), 0, (hipStream_t)stream, n, c, hw, L, a, wl, bl,
+                         out);
+    }
     FDTD_HIP(hipGetLastError());
   });
 }
