@@ -36,6 +36,8 @@ def shifted(a, dz, dy, dx):
     """b[k, j, i] = a[k+dz, j+dy, i+dx] inside the box, 0 outside."""
     nz, ny, nx = a.shape
     b = np.zeros_like(a)
+    if abs(dz) >= nz or abs(dy) >= ny or abs(dx) >= nx:
+        return b
     zs, ys, xs = slice(max(0, -dz), min(nz, nz - dz)), slice(max(0, -dy), min(ny, ny - dy)), slice(max(0, -dx), min(nx, nx - dx))
     zt, yt, xt = slice(max(0, dz), min(nz, nz + dz)), slice(max(0, dy), min(ny, ny + dy)), slice(max(0, dx), min(nx, nx + dx))
     b[zs, ys, xs] = a[zt, yt, xt]

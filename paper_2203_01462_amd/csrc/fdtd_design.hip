@@ -342,12 +342,12 @@ __global__ void __launch_bounds__(CB * CB) cascade_back_kernel(const CascadeBack
 }
 
 // The cell and LDS layout of a tiled single stage: a tile of tx x ty x tz
-// cells (a thread each) in a box with a halo of R (z: Rz) cells.
+// cells (a thread each) in a box with a halo of Rx, Ry, Rz cells.
 struct Tile {
-  int nx, ny, nz, R, Rz, tx, ty, tz;
-  __device__ __forceinline__ int sx() const { return tx + 2 * R; }
-  __device__ __forceinline__ int sy() const { return ty + 2 * R; }
-  __device__ __forceinline__ int sz() const { return tz + 2 * Rz; }
+  int nx, ny, nz, Rx, Ry, Rz, tx, ty, tz;
+  __host__ __device__ __forceinline__ int sx() const { return tx + 2 * Rx; }
+  __host__ __device__ __forceinline__ int sy() const { return ty + 2 * Ry; }
+  __host__ __device__ __forceinline__ int sz() const { return tz + 2 * Rz; }
 };
 
 // Calls fill(cell, k) -> value for every LDS cell k inside the box (cell: its
@@ -357,7 +357,7 @@ __device__ __forceinline__ void fill_tile(const Tile &g, double *lds, F &&fill) 
   const int sx = g.sx(), sy = g.sy(), cells = sx * sy * g.sz();
   for (int k = threadIdx.x; k < cells; k += blockDim.x) {
     const int r = k / sx, q = k - r * sx, p = r / sy;
-    const int jx = (int)blockIdx.x * g.tx - g.R + q, jy = (int)blockIdx.y * g.ty - g.R + (r - p * sy),
+    const int jx = (int)blockIdx.x * g.tx - g.Rx + q, jy = (int)blockIdx.y * g.ty - g.Ry + (r - p * sy),
               jz = (int)blockIdx.z * g.tz - g.Rz + p;
     const bool ok = jx >= 0 && jx < g.nx && jy >= 0 && jy < g.ny && jz >= 0 && jz < g.nz;
     lds[k] = ok ? fill(((int64_t)jz * g.ny + jy) * g.nx + jx) : 0.0;
@@ -369,7 +369,7 @@ __device__ __forceinline__ bool tile_cell(const Tile &g, int64_t &i, int &at) {
   const int t = threadIdx.x, lx = t % g.tx, ly = (t / g.tx) % g.ty, lz = t / (g.tx * g.ty);
   const int ix = blockIdx.x * g.tx + lx, iy = blockIdx.y * g.ty + ly, iz = blockIdx.z * g.tz + lz;
   i = ((int64_t)iz * g.ny + iy) * g.nx + ix;
-  at = ((lz + g.Rz) * g.sy() + ly + g.R) * g.sx() + lx + g.R;
+  at = ((lz + g.Rz) * g.sy() + ly + g.Ry) * g.sx() + lx + g.Rx;
   return ix < g.nx && iy < g.ny && iz < g.nz;
 }
 
@@ -548,7 +548,7 @@ struct fdtd_filter {
   DevBuf winv, xs[5], h, g[2];  // stage inputs x0..x3 and output x4; transpose scratch
   // the route by box and radius: all stages in one launch, one launch a stage
   // on tiles, or (3D beyond R = 4, whose halo exceeds the LDS, and boxes with
-  // more tiles along y or z than a grid has) the plain kernels
+  // more tiles than a grid has room for) the plain kernels
   enum { kCascade, kTiled, kPlain } route = kPlain;
   Tile tile{};
   int nt = 0;
@@ -588,7 +588,7 @@ dim3 tile_grid(const Tile &g) {
   return dim3((g.nx + g.tx - 1) / g.tx, (g.ny + g.ty - 1) / g.ty, (g.nz + g.tz - 1) / g.tz);
 }
 size_t tile_lds(const Tile &g) {
-  return (size_t)(g.tx + 2 * g.R) * (g.ty + 2 * g.R) * (g.tz + 2 * g.Rz) * sizeof(double);
+  return (size_t)g.sx() * g.sy() * g.sz() * sizeof(double);
 }
 
 template <typename T>
@@ -679,28 +679,53 @@ void filter_transpose(fdtd_filter *f, const void *gf, void *gout) {
 // single launch wins while three rounds of the CUs hold it (us per filter, cascade
 // against tiles: 300^2 14 / 22, 512^2 35 / 24).  Tiles of 256 cells where those of
 // 1024 would leave half of the CUs idle (100^2, R = 8:
-// 70 -> 47 us a filter).
+// 70 -> 47 us a filter).  Along an axis of few cells the tile is as short as the box
+// and longer along the others, and halo and taps keep inside the box (us per filter,
+// square tiles / these / the plain kernels, forward and transpose: 4000000 x 1,
+// R = 2 4922 / 248 / 461; 1000000 x 2, R = 3 1343 / 194 / 444).
 void filter_route(fdtd_filter *f) {
   const bool flat = f->nz == 1;
-  if ((!flat && f->R > 4) || f->ny > 500000 || f->nz > 500000) return;  // (65535 tiles along y and z)
+  if (!flat && f->R > 4) return;
   const int side = CB - 6 * f->R;  // (used up to R = 3)
   const bool cascade = flat && f->R <= CMAXR &&
                        (int64_t)((f->nx + side - 1) / side) * ((f->ny + side - 1) / side) <= 768;
   const bool small = f->n <= 131072;
-  f->route = cascade ? fdtd_filter::kCascade : fdtd_filter::kTiled;
-  f->tile = flat ? Tile{f->nx, f->ny, 1, f->R, 0, 32, 32, 1} : Tile{f->nx, f->ny, f->nz, f->R, f->Rz, 16, 8, 8};
-  if (small) f->tile = flat ? Tile{f->nx, f->ny, 1, f->R, 0, 16, 16, 1} : Tile{f->nx, f->ny, f->nz, f->R, f->Rz, 8, 8, 4};
-  const int sx = (f->route == fdtd_filter::kCascade ? CB : f->tile.tx) + 2 * f->R, sy = f->tile.ty + 2 * f->R;
-  std::vector<Tap> t;
-  for (int dz = -f->Rz; dz <= f->Rz; ++dz)
-    for (int dy = -f->R; dy <= f->R; ++dy)
-      for (int dx = -f->R; dx <= f->R; ++dx) {
-        const double w = f->r - std::sqrt((double)(dx * dx + dy * dy + dz * dz));
-        if (w > 0) t.push_back(Tap{w, (dz * sy + dy) * sx + dx, 0});
+  const int n[3] = {f->nx, f->ny, f->nz}, R[3] = {std::min(f->R, f->nx - 1), std::min(f->R, f->ny - 1),
+                                                  std::min(f->Rz, f->nz - 1)};
+  int t[3] = {flat ? (small ? 16 : 32) : (small ? 8 : 16), flat ? (small ? 16 : 32) : 8, flat ? 1 : (small ? 4 : 8)};
+  int spare = 1;
+  for (int d = 0; d < 3; ++d)
+    while (t[d] > 1 && t[d] / 2 >= n[d]) {
+      t[d] /= 2;
+      spare *= 2;
+    }
+  auto cells = [&] { return (t[0] + 2 * R[0]) * (t[1] + 2 * R[1]) * (t[2] + 2 * R[2]); };
+  for (int d = 0; d < 3; ++d)
+    while (spare > 1 && t[d] < n[d]) {
+      t[d] *= 2;
+      if (cells() > 8192) {  // 64 KiB of LDS
+        t[d] /= 2;
+        break;
       }
-  f->nt = (int)t.size();
-  f->taps.alloc(t.size() * sizeof(Tap));
-  FDTD_HIP(hipMemcpy(f->taps.p, t.data(), t.size() * sizeof(Tap), hipMemcpyHostToDevice));
+      spare /= 2;
+    }
+  f->tile = Tile{f->nx, f->ny, f->nz, R[0], R[1], R[2], t[0], t[1], t[2]};
+  const dim3 g = tile_grid(f->tile);
+  // (what a grid has room for: 65535 tiles along y and z, 2^32 threads along x)
+  const bool fits = g.y <= 65535 && g.z <= 65535 && (uint64_t)g.x * (t[0] * t[1] * t[2]) < (1ull << 32);
+  if (!cascade && !fits) return;
+  f->route = cascade ? fdtd_filter::kCascade : fdtd_filter::kTiled;
+  const int sx = cascade ? CB + 2 * f->R : f->tile.sx(), sy = f->tile.sy();
+  std::vector<Tap> taps;
+  for (int dz = -R[2]; dz <= R[2]; ++dz)
+    for (int dy = -R[1]; dy <= R[1]; ++dy)
+      for (int dx = -R[0]; dx <= R[0]; ++dx) {
+        const double w = f->r - std::sqrt((double)(dx * dx + dy * dy + dz * dz));
+        if (w > 0) taps.push_back(Tap{w, (dz * sy + dy) * sx + dx, 0});
+      }
+  f->nt = (int)taps.size();
+  f->taps.alloc(taps.size() * sizeof(Tap));
+  FDTD_HIP(hipMemcpy(f->taps.p, taps.data(), taps.size() * sizeof(Tap), hipMemcpyHostToDevice));
 }
 
 }  // namespace
