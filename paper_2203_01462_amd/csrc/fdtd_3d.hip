@@ -1124,12 +1124,27 @@ std::vector<int> gen3d_plan(const Step3D<T> &p, int &nS, int &nM, int &nD, int &
 // A chunk recomputes the H of the plane below it: four planes where that leaves
 // four workgroups a CU, else two for a shorter chain (FP32 48^3 15.5 / 13.7 with
 // four; 160^3 54 / 62 with two).
+// Where a design chunk meets the absorber (a side of few tiles, a deep absorber)
+// every workgroup is launched with the registers of the design body with all
+// absorber axes, so fewer are in flight; the lists pay that in their design list
+// alone.  That costs the adjoint, and the FP64 forward, more than the launches
+// once there are chunks enough to fill the chip many times; later where much
+// of the grid meets several absorber axes, whose list is slow as well.
+// us per step, lists against one launch (chunks of four planes, share of several
+// axes):
+//   FP32 adjoint  64x200x200 (2500) 57, 53   40x240x240 (3600) 64, 68
+//        24x500x500 (7875) 118, 131   160^3 with 32 cells (4000, most) 141, 125
+//   FP64 adjoint  112^3 with 24 cells (1568, most) 122, 109   40x160x160 (1600) 71, 76
+//        24x250x250 (2016) 81, 104   160^3 with 32 cells 275, 293
+//   FP64 forward  24x250x250 78, 77   48x250x250 (4032) 182, 189   40x350x350 (7744)
+//        8 % less by the lists; 160^3 with 32 cells 245, 215
 template <typename T>
-std::vector<int> whole3d_plan(const Step3D<T> &p, int &kc, int &axD) {
+std::vector<int> whole3d_plan(const Step3D<T> &p, int &kc, int &axD, int &use) {
   const int nx = p.n[0], ny = p.n[1], nz = p.n[2];
   if ((int64_t)nx * ny * nz * 12 * (int64_t)sizeof(T) > (int64_t)512 << 20) return {};
   kc = (int64_t)((nx + TX - 1) / TX) * ((ny + TY - 1) / TY) * ((nz + 3) / 4) >= 1024 ? 4 : 2;
   axD = 0;
+  int64_t several = 0;
   const int nbx = (nx + TX - 1) / TX, nby = (ny + TY - 1) / TY, nbz = (nz + kc - 1) / kc;
   std::vector<int> codes, group, work;
   for (int bz = 0; bz < nbz; ++bz)
@@ -1141,6 +1156,7 @@ std::vector<int> whole3d_plan(const Step3D<T> &p, int &kc, int &axD) {
         int ax = tile_axes(p, tl);
         for (int k = std::max(tl.kb - 1, 0); k < tl.ke; ++k) ax |= plane_axes(p, k);
         int v = ax == 1 ? 0 : ax == 2 ? 1 : ax == 4 ? 2 : ax == 0 ? 3 : 4;
+        several += v == 4;
         if (design_chunk(p, tl)) {
           v = 5;
           axD |= ax;
@@ -1149,6 +1165,15 @@ std::vector<int> whole3d_plan(const Step3D<T> &p, int &kc, int &axD) {
         group.push_back(bz * ((nby + 3) / 4) + by / 4);
         work.push_back(tl.ke - tl.kb + 1);
       }
+  use = 3;
+  if (axD) {
+    constexpr bool f64 = std::is_same<T, double>::value;
+    const bool most = 3 * several > (int64_t)codes.size();
+    const int64_t chunks = (int64_t)nbx * nby * ((nz + 3) / 4);
+    if (chunks > (f64 ? (most ? 2900 : 1200) : (most ? 6000 : 3100))) use &= ~2;
+    if (f64 && chunks > (most ? 8000 : 4000)) use &= ~1;
+  }
+  if (use == 0) return {};
   return xcd_order(codes, group, work);
 }
 
@@ -1329,7 +1354,7 @@ void launch_step3d(const Step3D<T> &p, T *rd, T *wr, int n, bool adjoint, hipStr
   Step3D<T> q = p;  // copy 0 is read, copy 1 written
   q.A[0] = rd;
   q.A[1] = wr;
-  if (q.gW > 0) {
+  if (q.gW > 0 && (q.gWuse & (adjoint ? 2 : 1))) {
     if (adjoint && q.gWD) hipLaunchKernelGGL((step3d_whole<T, true, true>), dim3(q.gW), dim3(NT), 0, s, q, n, q.wlist);
     else if (adjoint) hipLaunchKernelGGL((step3d_whole<T, true, false>), dim3(q.gW), dim3(NT), 0, s, q, n, q.wlist);
     else if (q.gWD) hipLaunchKernelGGL((step3d_whole<T, false, true>), dim3(q.gW), dim3(NT), 0, s, q, n, q.wlist);
@@ -1372,8 +1397,8 @@ void plain3d_box(const Step3D<T> &p, int pb[6]) {
 
 template std::vector<int> gen3d_plan<float>(const Step3D<float> &, int &, int &, int &, int &);
 template std::vector<int> gen3d_plan<double>(const Step3D<double> &, int &, int &, int &, int &);
-template std::vector<int> whole3d_plan<float>(const Step3D<float> &, int &, int &);
-template std::vector<int> whole3d_plan<double>(const Step3D<double> &, int &, int &);
+template std::vector<int> whole3d_plan<float>(const Step3D<float> &, int &, int &, int &);
+template std::vector<int> whole3d_plan<double>(const Step3D<double> &, int &, int &, int &);
 template void plain3d_box<float>(const Step3D<float> &, int *);
 template void plain3d_box<double>(const Step3D<double> &, int *);
 template void launch_step3d<float>(const Step3D<float> &, float *, float *, int, bool, hipStream_t, const Aux3D &);

@@ -90,10 +90,11 @@ struct Step3D {
   const int *glist;
   int gS, gM, gD, gAxD;
   // One launch a step (small grids): the list of all tile-chunks of kc planes
-  // (from whole3d_plan), its length and whether a design chunk meets the
-  // absorber; gW = 0: the lists above and the plain launch.
+  // (from whole3d_plan), its length (0: none), whether a design chunk meets the
+  // absorber and the directions that take it (bit 0 forward, bit 1 adjoint);
+  // the others take the lists above and the plain launch.
   const int *wlist;
-  int gW, gWD, kc;
+  int gW, gWD, kc, gWuse;
   int pb[6];  // bounding box of the plain tile-planes: origin x, y, z, extent x, y, z (from plain3d_box)
   // Two-step blocking of the plain background (see plan3d_super): the grid of
   // super-chunks (origin so, chunk counts sn), one flag byte per chunk
@@ -130,11 +131,11 @@ template <typename T>
 std::vector<int> gen3d_plan(const Step3D<T> &p, int &nS, int &nM, int &nD, int &axD);
 
 // Every tile-chunk of kc planes with the body it takes (code 8c + v: v = 0, 1, 2
-// one absorber axis, 3 none, 4 several, 5 design without, 6 design with
-// absorber), in the order of gen3d_plan; empty when the grid takes the lists
-// above.  axD: a design chunk meets the absorber.
+// one absorber axis, 3 none, 4 several, 5 design), in the order of gen3d_plan;
+// empty when both directions take the lists above.  axD: a design chunk meets
+// the absorber; use: the directions that take it (gWuse above).
 template <typename T>
-std::vector<int> whole3d_plan(const Step3D<T> &p, int &kc, int &axD);
+std::vector<int> whole3d_plan(const Step3D<T> &p, int &kc, int &axD, int &use);
 
 // Bounding box of the tile-planes that take the plain update (extent 0
 // when there are none); the plain launch covers only this box.

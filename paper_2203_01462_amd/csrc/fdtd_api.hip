@@ -60,7 +60,7 @@ struct fdtd_ctx {
   DevBuf glist3;  // 3D: tile-chunk lists of the general update
   int gS = 0, gM = 0, gD = 0, gAxD = 0;  // lengths of the three lists in glist3
   DevBuf wlist3;  // 3D, one launch a step: all tile-chunks
-  int gW = 0, gWD = 0, kc3 = 0;
+  int gW = 0, gWD = 0, kc3 = 0, gWuse = 0;
   // 3D two-step blocking of the plain background (FP32): the super-chunk
   // launch list and flag grid; with super-chunks the state rotates over
   // three arenas (the state after s steps lives in arena s mod 3)
@@ -509,7 +509,7 @@ void fill_params3d(fdtd_ctx *c, Step3D<T> &p, bool rerun) {
     c->gS = nS; c->gM = nM; c->gD = nD; c->gAxD = axD;
     // (the variable, set, asks for one of the two schedules over those lists)
     if (!std::getenv("FDTD_TEMPORAL_BLOCKING")) {
-      const std::vector<int> all = whole3d_plan(p, c->kc3, c->gWD);
+      const std::vector<int> all = whole3d_plan(p, c->kc3, c->gWD, c->gWuse);
       c->gW = (int)all.size();
       if (c->gW > 0) {
         upload(c->stream, c->wlist3, all);
@@ -518,7 +518,7 @@ void fill_params3d(fdtd_ctx *c, Step3D<T> &p, bool rerun) {
     }
   }
   p.wlist = c->wlist3.as<int>();
-  p.gW = c->gW; p.gWD = c->gWD; p.kc = c->kc3;
+  p.gW = c->gW; p.gWD = c->gWD; p.kc = c->kc3; p.gWuse = c->gWuse;
   p.glist = c->glist3.as<int>();
   p.gS = c->gS; p.gM = c->gM; p.gD = c->gD; p.gAxD = c->gAxD;
   plain3d_box(p, p.pb);

@@ -48,3 +48,18 @@ def test_one_launch_step_matches_lists(gpu, prec, n, pml, m, dlo, dn, glo, gn, s
     assert abs(F1 - F0) <= tf * abs(F0)
     assert np.linalg.norm(s1 - s0) <= tf * np.linalg.norm(s0)
     assert np.linalg.norm(g1 - g0) <= tg * np.linalg.norm(g0)
+
+
+# A design in the absorber's tiles: from about 1200 (FP64) and 3100 (FP32) chunks of
+# 32 x 8 x 4 nodes the adjoint takes the lists and the forward one launch, from 4000
+# the FP64 forward the lists too.
+THIN = [
+    ((40, 160, 164), 5, 3, (14, 60, 60), (12, 20, 22), (19, 70, 70), (2, 2, 2), 12, 0),
+    ((24, 402, 322), 3, 2, (8, 200, 150), (8, 30, 30), (11, 212, 164), (2, 2, 2), 13, 5),
+]
+
+
+@pytest.mark.parametrize("prec", [64, 32])
+@pytest.mark.parametrize("n,pml,m,dlo,dn,glo,gn,steps,ckpt", THIN)
+def test_thin_grid_mixes_the_two(gpu, prec, n, pml, m, dlo, dn, glo, gn, steps, ckpt):
+    test_one_launch_step_matches_lists(gpu, prec, n, pml, m, dlo, dn, glo, gn, steps, ckpt)
