@@ -35,6 +35,9 @@ constexpr int TM = 64, TN = 64, TK = 16, PAD = 4;
 // XCD b % 8 takes items (b % 8) * grid / 8 onwards, in order.
 __device__ __forceinline__ int xcd_item(int b, int grid) { return (b & 7) * (grid >> 3) + (b >> 3); }
 unsigned xcd_grid(int64_t items) { return (unsigned)((items + 7) / 8 * 8); }
+// A launch takes fewer than 2^32 work items along an axis: so many workgroups of BS
+// at most in such a grid.
+constexpr int64_t MAX_XCD = ((int64_t)1 << 32) / BS - 8;
 
 // IEEE binary32 -> bfloat16, round to nearest even (NaN kept quiet).
 __device__ __forceinline__ uint16_t f2bf(float f) {
@@ -606,6 +609,7 @@ bool conv_packs(int n, int cin, int cout, int h, int w) {
   const double packed = images * (((int64_t)h * w + TN - 1) / TN);
   const double tiled = images * ((h + GT - 1) / GT) * ((w + GT - 1) / GT);
   const int steps = (9 * cin + 15) / 16, padded = 9 * ((cin + 15) / 16);
+  if (tiled > (double)MAX_XCD) return true;  // (more tiles than a one-dimensional grid takes)
   const double step = cin % 4 == 0 ? 0.115 : cout > 32 ? 0.4 : 0.21;
   return std::max(1.0, packed / 896) * (steps + 0.4) < std::max(1.0, tiled / 512) * (0.6 + step * padded);
 }
@@ -640,9 +644,9 @@ void launch_conv(int n, int cin, int cout, int h, int w, const uint16_t *x, cons
                        z, a, mask);
     return;
   }
-  if (cin % CC == 0 && h % TT == 0 && w % TT == 0 && ((uintptr_t)wt & 15) == 0) {
-    const int tiles = (h / TT) * (w / TT);
-    const dim3 g(xcd_grid((int64_t)tiles * ((cout + 16 * MT - 1) / (16 * MT)) * n));
+  const int64_t items = (int64_t)(h / TT) * (w / TT) * ((cout + 16 * MT - 1) / (16 * MT)) * n;
+  if (cin % CC == 0 && h % TT == 0 && w % TT == 0 && ((uintptr_t)wt & 15) == 0 && items <= MAX_XCD) {
+    const dim3 g(xcd_grid(items));
     const bool odd = (uintptr_t)x & 15;
     const size_t nx = (size_t)cin * n * h * w, ny = (size_t)cout * n * h * w;
     // in place: neighbouring tiles still read what this one writes

@@ -76,3 +76,27 @@ def test_convolution_in_place(nn, n, cin, cout, h, w):  # noqa: F811
     nn.conv3x3_dgrad(part, None, wt, dz, n, cout, cin, h, w)
     torch.cuda.synchronize()
     assert torch.equal(dz[:cout * px].cpu(), z.cpu())
+
+
+def test_more_tiles_than_a_one_dimensional_grid_takes(nn):  # noqa: F811
+    """65535 images of 128 x 136: 2^24 tiles and more.  Whole numbers, so every order of
+    the sums gives the same bits: repeats of 64 images give repeats of their result."""
+    n, cin, h, w, r = 65535, 4, 128, 136, 64
+    if torch.cuda.mem_get_info()[0] < 20 << 30:
+        pytest.skip("20 GiB of device memory")
+    g = torch.Generator().manual_seed(1)
+    px = h * w
+    part = T.bits(torch.randint(-3, 4, (cin, r, px), generator=g).float())
+    wt = T.bits(torch.randint(-2, 3, (1, 9 * cin), generator=g).float())
+    want = torch.empty(r * px, dtype=torch.int16, device="cuda")
+    nn.conv3x3(part, wt, None, r, cin, 1, h, w, a=want)
+    x = torch.empty(cin, n, px, dtype=torch.int16, device="cuda")
+    for i in range(0, n, r):
+        x[:, i:i + r] = part[:, :min(r, n - i)]
+    a = torch.empty(n * px, dtype=torch.int16, device="cuda")
+    nn.conv3x3(x.reshape(-1), wt, None, n, cin, 1, h, w, a=a)
+    torch.cuda.synchronize()
+    assert int((want != 0).sum()) > 0
+    for i in range(0, n, r):
+        m = min(r, n - i)
+        assert torch.equal(a[i * px:(i + m) * px], want[:m * px]), i
