@@ -226,8 +226,10 @@ fdtd_status fdtd_destroy(fdtd_ctx *ctx);
  * depth 2 the plain background's super-tiles advance two steps per pass,
  * everything else one step per launch, two launches per pair of steps for all
  * instances together.  The N steps of a forward (or adjoint) solve are captured once
- * into a HIP graph and replayed.  Every instance computes exactly what a
- * single context with the same config and tile depth computes.
+ * into a HIP graph and replayed.  An FP64 instance computes exactly what a
+ * single context with the same config computes.  In FP32 a single context takes
+ * several steps per launch, a batch does not, and the two kernels round
+ * differently (objectives differ by about 1e-8 of their value).
  */
 typedef struct fdtd_batch fdtd_batch; /* opaque */
 
@@ -272,13 +274,14 @@ fdtd_status fdtd_batch_adjoint(fdtd_batch *b);
 /* dF/drho of instance `index` (as fdtd_gradient). */
 fdtd_status fdtd_batch_gradient(fdtd_batch *b, int32_t index, void *grad_out, int64_t count, int32_t on_device);
 
-/* Tile depth used for instance `index` (2 with several steps per launch), and
- * the event time (ms) of the last
+/* Tile depth used for instance `index` (nodes per thread along y: with several
+ * steps per launch 2 or 4, the same for all), and the event time (ms) of the last
  * batched forward and adjoint step sequences (all instances together). */
 fdtd_status fdtd_batch_info(fdtd_batch *b, int32_t index, int32_t *rows_out, double *forward_ms, double *adjoint_ms);
 
-/* Temporal-block depth (1 or 2) used for instance `index`; with several steps
- * per launch 2 when it has super-tiles. */
+/* Temporal-block depth used for instance `index`: 1 = one step per launch, 2 =
+ * several (two over the super-tiles of the blocked schedule; all nodes of every
+ * instance in FP64 with rows = 0 and depth = 0). */
 fdtd_status fdtd_batch_depth(fdtd_batch *b, int32_t index, int32_t *depth_out);
 
 /* Release the batch and all instances.  NULL is accepted. */

@@ -56,7 +56,6 @@ struct fdtd_ctx {
   // a batch's two-step blocking of the plain background: a third copy of the
   // fields, the super-tiles and the per-step tiles
   DevBuf fld3[3], tbTiles, tbRest;
-  int super_tiles = 0;  // super-tiles the grid has room for (what fdtd_batch_depth reports)
   DevBuf glist3;  // 3D: tile-chunk lists of the general update
   int gS = 0, gM = 0, gD = 0, gAxD = 0;  // lengths of the three lists in glist3
   DevBuf wlist3;  // 3D, one launch a step: all tile-chunks
@@ -247,8 +246,8 @@ void deal_to_xcds(std::vector<int> &v, int lo, int hi, G group) {
 // FDTD_TEMPORAL_BLOCKING=0 turns it off, =1 on; unset, 2D contexts use it and
 // 3D contexts do not (two steps of the plain background's super-chunks:
 // bit-identical but slower on the 256^3 workload, whose plain background is
-// half the grid and a third of the step time).  Both schedules give the same
-// results.
+// half the grid and a third of the step time).  The schedules compute the same
+// sums: FP64 2D bit for bit, FP32 up to the rounding of separately compiled kernels.
 bool blocking_enabled(int dims) {
   const char *v = std::getenv("FDTD_TEMPORAL_BLOCKING");
   if (v && v[0] == '0') return false;
@@ -318,12 +317,6 @@ void create_2d(fdtd_ctx *c, Kind2D kind) {
     }
   }
   if (c->prec == 32) build_axis_tables<float>(c); else build_axis_tables<double>(c);
-  const int dbox[4] = {g.design_lo[0], g.design_lo[1], g.design_n[0], g.design_n[1]};
-  const int gbox[4] = {g.gap_lo[0], g.gap_lo[1], g.gap_n[0], g.gap_n[1]};
-  // without a plane wave there are no injection lines to keep clear
-  Tb2dPlan pl = tf ? tb2d_plan(c->nx, c->ny, P, c->ia, c->ib, c->ja, c->jb, dbox, gbox)
-                   : tb2d_plan(c->nx, c->ny, P, -8, -8, -8, -8, dbox, gbox);
-  c->super_tiles = (int)pl.tb.size();
   // (the several-step kernel indexes a field with 32 bits)
   c->multi = kind == Kind2D::kMulti && blocking_enabled(2) && (int64_t)c->pitch * c->ny < INT32_MAX;
   // (... and updates every design and gap edge: TEz boxes that reach a PEC wall, which
@@ -336,7 +329,13 @@ void create_2d(fdtd_ctx *c, Kind2D kind) {
     const int n2d[1][2] = {{c->nx, c->ny}};
     c->mt = c->te ? multi_te_tile(c->nx, c->ny, c->prec) : multi2d_tile(n2d, 1, c->prec);
   }
-  if (!pl.tb.empty() && kind == Kind2D::kBlocked && blocking_enabled(2) && !c->te) {
+  if (kind != Kind2D::kBlocked || !blocking_enabled(2) || c->te) return;
+  const int dbox[4] = {g.design_lo[0], g.design_lo[1], g.design_n[0], g.design_n[1]};
+  const int gbox[4] = {g.gap_lo[0], g.gap_lo[1], g.gap_n[0], g.gap_n[1]};
+  // without a plane wave there are no injection lines to keep clear
+  Tb2dPlan pl = tf ? tb2d_plan(c->nx, c->ny, P, c->ia, c->ib, c->ja, c->jb, dbox, gbox)
+                   : tb2d_plan(c->nx, c->ny, P, -8, -8, -8, -8, dbox, gbox);
+  if (!pl.tb.empty()) {
     // the interior super-tiles run one launch early (beside the rest tiles'
     // second step of the previous pair), the border ones after them
     std::vector<int> order;
@@ -1460,7 +1459,7 @@ void batch_setup(fdtd_batch *b) {
     upload(b->stream, b->mparams, ms);
     upload(b->stream, b->mfirst, first);
     FDTD_HIP(hipStreamSynchronize(b->stream));
-    b->rows.assign(cnt, 2);
+    b->rows.assign(cnt, b->mt.R);
     b->tb.assign(cnt, 0);
     return;
   }
@@ -1793,10 +1792,9 @@ fdtd_status fdtd_batch_create(const fdtd_config *cfgs, int32_t count, const fdtd
     for (int k = 0; k < 4; ++k) FDTD_HIP(hipEventCreate(&b->ev[k]));
     b->prec = cfgs[0].precision;
     b->N = cfgs[0].n_steps;
-    // FP32 batches keep their own kernels, although several steps per launch
-    // took 12 instead of 40 us per step for 16 instances of sides 128-1024:
-    // those kernels are compiled to other roundings than the single
-    // contexts' (F differs by ~1e-8), and a batch's results stay its own.
+    // FP32 batches take the per-step and the blocked kernel: several steps per
+    // launch, measured at 12 us per step instead of 40 for 16 instances of sides
+    // 128-1024, are compiled to other roundings (F differs by ~1e-8).
     b->multi = b->prec == 64 && b->opt.rows == 0 && b->opt.depth == 0 && blocking_enabled(2);
     for (int k = 0; k < count; ++k)  // as in create_2d
       b->multi = b->multi && (((int64_t)cfgs[k].n[0] + 63) & ~63ll) * cfgs[k].n[1] < INT32_MAX;
@@ -1900,7 +1898,7 @@ fdtd_status fdtd_batch_depth(fdtd_batch *b, int32_t index, int32_t *depth_out) {
   return bguard(b, [&] {
     fdtd_ctx *c = instance(b, index);
     if (!depth_out) throw einval("null depth pointer");
-    *depth_out = (b->multi ? c->super_tiles > 0 : b->mix && b->tb[index] && c->nTb > 0) ? 2 : 1;
+    *depth_out = b->multi || (b->mix && b->tb[index] && c->nTb > 0) ? 2 : 1;
   });
 }
 
