@@ -270,7 +270,7 @@ class UNet:
         # backward buffers: FP32 gradients of activations, BF16 gradients of pre-activations
         big = max(c * n * sz[l] ** 2 for l, c in enumerate(ch))
         self.ga = torch.empty(big, **f32)
-        self.gb = torch.empty(big, **f32)
+        self.gb = torch.empty(self.bottom.numel(), **f32)  # the linear head's share of the bottom gradient
         # gradient of each decoder concat buffer; its skip half is consumed by the encoder pass
         self.gcat = [torch.empty((ch[l + 1] + ch[l]) * n * sz[l] ** 2, **f32) for l in range(L - 1)]
         self.gz = torch.empty(max(big, n * s * s), **bf)
