@@ -42,20 +42,20 @@ SRC_3D = ["paper_2203_01462_amd/csrc/fdtd_3d.hip", "paper_2203_01462_amd/csrc/fd
 SRC_TE = ["paper_2203_01462_amd/csrc/fdtd_te_multi.hip", "paper_2203_01462_amd/csrc/fdtd_multi.hpp", "paper_2203_01462_amd/csrc/fdtd_api.hip"]
 MEASURED_TRAFFIC = {
     # one launch = eight time steps of the grid
-    "tmz2d_2048_fp32": {"sources": SRC_2D, "sha256_16": "655ba62768e8d035",
+    "tmz2d_2048_fp32": {"sources": SRC_2D, "sha256_16": "f3d92ea55c2a1435",
                         "fwd": 26.5e6, "adj": 29.4e6,
                         "profile": "profiles/step2d_multi_tmz2d_2048_fp32.md"},
     # one time step of all 64 instances = one step2d_batch_mix_kernel launch
-    "tmz2d_batch64_c4": {"sources": SRC_BATCH, "sha256_16": "b410919b417b3e4e",
-                         "fwd": 500.1e6, "adj": 521.8e6,
+    "tmz2d_batch64_c4": {"sources": SRC_BATCH, "sha256_16": "533bf3d697cc0670",
+                         "fwd": 500.2e6, "adj": 521.8e6,
                          "profile": "profiles/step2d_batch_mix_kernel_tmz2d_batch64_c4.md"},
     # one time step = the general update (forward: one step3d_general_fwd
     # launch; adjoint: three step3d_general launches) + step3d_plain
-    "yee3d_256_fp32": {"sources": SRC_3D, "sha256_16": "d944e5384d7281f8",
-                       "fwd": 1303.9e6, "adj": 1337.3e6,
+    "yee3d_256_fp32": {"sources": SRC_3D, "sha256_16": "4973fd2646a1758d",
+                       "fwd": 1303.7e6, "adj": 1337.4e6,
                        "profile": "profiles/step3d_yee3d_256_fp32.md"},
     # one launch = eight time steps of the grid
-    "te2d_2048_fp32": {"sources": SRC_TE, "sha256_16": "964230abdae8a089",
+    "te2d_2048_fp32": {"sources": SRC_TE, "sha256_16": "3577d4f00a6f53a3",
                        "fwd": 40.7e6, "adj": 50.9e6,
                        "profile": "profiles/step_te_multi_te2d_2048_fp32.md"},
 }

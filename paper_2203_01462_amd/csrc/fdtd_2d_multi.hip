@@ -521,7 +521,9 @@ int step2d_multi_blocks(int nx, int ny, const MultiTile &g) { return multi_regio
 // instructions per step and wavefront, and more steps per launch pay for the
 // launch and the loads), so the candidates are tried in that order.  Beyond
 // one round the work per exact node counts, and the bytes of the halos: 64 x 64
-// nodes in FP32, 64 x 32 in FP64 (R = 4 on 12 or 16 wavefronts spills there).
+// nodes in FP32, 64 x 32 in FP64.  (FP64 at R = 4 spills, 46 registers forward and
+// 138 adjoint; compiled for 8 wavefronts at most it does not, but then one
+// workgroup is on a CU instead of two: 2048^2 10.8 / 11.8 -> 15.7 / 15.7.)
 // Measured on square grids with a side/4 design box, us per forward / adjoint
 // step (R, nw, K), where the neighbouring choices cross:
 //   FP32 333^2: 2,16,10 1.10 / 1.04; 4,8,8 1.26 / 1.23; 4,16,12 1.32 / 1.48

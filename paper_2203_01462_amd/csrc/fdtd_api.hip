@@ -247,7 +247,7 @@ void deal_to_xcds(std::vector<int> &v, int lo, int hi, G group) {
 // 3D contexts do not (two steps of the plain background's super-chunks:
 // bit-identical but slower on the 256^3 workload, whose plain background is
 // half the grid and a third of the step time).  The schedules compute the same
-// sums: FP64 2D bit for bit, FP32 up to the rounding of separately compiled kernels.
+// sums, FP64 TMz to the last bit, else up to the rounding of separately compiled code.
 bool blocking_enabled(int dims) {
   const char *v = std::getenv("FDTD_TEMPORAL_BLOCKING");
   if (v && v[0] == '0') return false;

@@ -10,7 +10,8 @@
 //
 // What bounds it is what bounds the TMz kernel.  A launch per step before
 // (fdtd_te.hip): 384^2 FP32 11.7 / 13.4 us per forward / adjoint step, now 1.5 /
-// 1.75; 1024^2 FP32 18.5, now 3.7.  The results keep their bits.
+// 1.75; 1024^2 FP32 18.5, now 3.7.  The sums are that kernel's, up to the rounding
+// of separately compiled code.
 #include <algorithm>
 
 #include "fdtd_multi.hpp"
@@ -499,7 +500,9 @@ __global__ void __launch_bounds__(64 * MWMAX)
 // Regions by size, as in fdtd_2d_multi.hip: the flattest that one round of the
 // 256 CUs holds; beyond that 64 x 32 regions with fewer halo nodes, on half the
 // wavefronts once the work per node counts more than the adjoint's spilled
-// registers (FP32, R = 4).  us per forward / adjoint step (R, nw, K):
+// registers (91 in FP32 with R = 4; compiled without spills for 8 wavefronts at
+// most the 2048^2 adjoint takes 13.1 us instead of 8.9).  us per forward / adjoint
+// step (R, nw, K):
 //   FP32  256^2: 2,16,10 1.30 / 1.58; 2,16,8 1.46 / 1.70
 //         384^2: 2,16,10 1.78 / 1.59; 2,16,8 1.51 / 1.75; 4,8,8 1.92 / 2.29
 //         700^2: 2,16,8  3.07 / 2.52; 4,8,8 2.56 / 3.31
