@@ -1482,12 +1482,14 @@ __global__ void __launch_bounds__(BS) gap_linear_back_a_kernel(int nimg, int c, 
 }
 
 // out[n] = bl + sum_c wl[c] mean_p a[c][n][p]: a workgroup per image (or several, one
-// after another), FP64 sums in a fixed order.  From 64 pixels on (SMALL false) a
-// wavefront takes a channel, then the next one, its lanes the pixels lane + 64 k;
-// below, L lanes a channel and 64 / L channels side by side.  256 channels of 13 x 13
-// pixels, 32 images: 10 us (40 with 256 threads that divide an index per element);
-// 64 channels of one pixel, 4096 images: 8 (21 with 64 lanes per channel).
-template <bool SMALL>
+// after another), FP64 sums in a fixed order.  Q = 1: a wavefront takes a channel, then
+// the next one, its lanes the pixels lane + 64 k; Q = 4 (64 to 255 pixels): four
+// channels at a time, for loads in flight; Q = 0 (fewer): L lanes a channel and 64 / L
+// channels side by side.  256 channels of 13 x 13 pixels, 32 images: 8 us (40 with 256
+// threads that divide an index per element); 64 channels of one pixel, 4096 images:
+// 8 (21 with 64 lanes per channel), of 10 x 10 pixels 24 (Q = 1 36); 256 channels of
+// 16 x 16, 1024 images: Q = 4 53, Q = 1 31.
+template <int Q>
 __global__ void __launch_bounds__(1024) gap_linear_kernel(int nimg, int c, int hw, int L, const uint16_t *__restrict__ a,
                                                            const float *__restrict__ wl, const float *__restrict__ bl,
                                                            float *__restrict__ out) {
@@ -1495,20 +1497,33 @@ __global__ void __launch_bounds__(1024) gap_linear_kernel(int nimg, int c, int h
   const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63, waves = blockDim.x >> 6;
   for (int n = blockIdx.x; n < nimg; n += gridDim.x) {
     double v = 0;
-    if constexpr (SMALL) {
+    if constexpr (Q == 0) {
       const int side = 64 / L, p = lane & (L - 1);
       if (p < hw) {
 #pragma unroll 4
         for (int ch = wv * side + lane / L; ch < c; ch += waves * side)
           v += (double)wl[ch] * (double)bf2f(a[((size_t)ch * nimg + n) * hw + p]);
       }
-    } else {
-      for (int ch = wv; ch < c; ch += 16) {
+    } else if constexpr (Q == 1) {
+      for (int ch = wv; ch < c; ch += waves) {
         const uint16_t *row = a + ((size_t)ch * nimg + n) * hw;
         double sp = 0;
 #pragma unroll 4
         for (int p = lane; p < hw; p += 64) sp += bf2f(row[p]);
         v += (double)wl[ch] * sp;
+      }
+    } else {
+      for (int ch = wv; ch < c; ch += Q * waves) {
+        const uint16_t *row[Q];
+        double sp[Q] = {};
+#pragma unroll
+        for (int q = 0; q < Q; ++q) row[q] = a + ((size_t)std::min(ch + q * waves, c - 1) * nimg + n) * hw;
+        for (int p = lane; p < hw; p += 64)
+#pragma unroll
+          for (int q = 0; q < Q; ++q) sp[q] += bf2f(row[q][p]);
+#pragma unroll
+        for (int q = 0; q < Q; ++q)
+          if (ch + q * waves < c) v += (double)wl[ch + q * waves] * sp[q];
       }
     }
     for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, 64);
@@ -1516,7 +1531,7 @@ __global__ void __launch_bounds__(1024) gap_linear_kernel(int nimg, int c, int h
     __syncthreads();
     if (threadIdx.x == 0) {
       double s = 0;
-      for (int k = 0; k < (SMALL ? waves : 16); ++k) s += lds[k];
+      for (int k = 0; k < waves; ++k) s += lds[k];
       out[n] = (float)(s / hw + bl[0]);
     }
     if (n + (int)gridDim.x < nimg) __syncthreads();
@@ -1876,16 +1891,15 @@ fdtd_status fdtd_nn_gap_linear(int32_t n, int32_t c, int32_t hw, const uint16_t 
     int L = 1;
     while (L < 64 && L < hw) L *= 2;
     const dim3 grid(std::min(n, 1 << 21));
-    if (hw >= 64) {
-      hipLaunchKernelGGL(gap_linear_kernel<false>, grid, dim3(1024), 0, (hipStream_t)stream, n, c, hw, L, a, wl, bl, out);
-    } else {
-      // while two workgroups a CU hold the images, the more wavefronts the better; beyond,
-      // their number costs (4096 images of 64 channels, 9 pixels: 22 us with 1024
-      // threads)
-      const int threads = (int)std::min<int64_t>(n <= 512 ? 1024 : 256, ((int64_t)c * L + 63) / 64 * 64);
-      hipLaunchKernelGGL(gap_linear_kernel<true>, grid, dim3(threads), 0, (hipStream_t)stream, n, c, hw, L, a, wl, bl,
-                         out);
-    }
+    // while two workgroups a CU hold the images, the more wavefronts the better; beyond,
+    // their number costs, unless each still has much to do (4096 images of 64 channels:
+    // 9 pixels 22 us with 1024 threads, 8 with 256; 100 pixels 28 with 512, 24 with 256;
+    // 1024 images of 256 channels, 169 pixels 27 with 512, 42 with 256; 256 pixels 33
+    // with 1024, 31 with 512)
+    const int most = n <= 512 ? 1024 : hw >= 256 || (hw >= 64 && c > 64) ? 512 : 256;
+    const int threads = (int)std::min<int64_t>(most, ((int64_t)c * L + 63) / 64 * 64);
+    auto *k = hw < 64 ? &gap_linear_kernel<0> : hw < 256 ? &gap_linear_kernel<4> : &gap_linear_kernel<1>;
+    hipLaunchKernelGGL(k, grid, dim3(threads), 0, (hipStream_t)stream, n, c, hw, L, a, wl, bl, out);
     FDTD_HIP(hipGetLastError());
   });
 }

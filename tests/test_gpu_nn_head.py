@@ -24,3 +24,11 @@ def test_gap_linear(nn, n, c, hw):  # noqa: F811
     mag = torch.einsum("c,cnp->n", wl.double().abs(), a.double().abs()) / hw + bl.double().abs()
     ulp = 2.0 ** (torch.floor(torch.log2(want.abs().clamp_min(1e-30))) - 23)
     assert ((out.cpu().double() - want).abs() <= 0.5 * ulp + 2.0 ** -45 * mag).all()
+
+
+# 64 to 255 pixels (four channels at a time: fewer and more than the wavefronts hold),
+# 256 and more, each with few images and beyond 512
+@pytest.mark.parametrize("n,c,hw", [(513, 3, 64), (600, 70, 100), (520, 64, 255), (2, 200, 130), (513, 13, 256),
+                                     (600, 65, 300)])
+def test_gap_linear_of_many_images(nn, n, c, hw):  # noqa: F811
+    test_gap_linear(nn, n, c, hw)
